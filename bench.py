@@ -177,6 +177,10 @@ def main():
     desc = json.loads(plan.describe())
     sweep_kernel = "k_cd_panel_la" if desc.get("schedule") == "lookahead" else (
         "k_cd_panel" if desc.get("engine") == "panel" else "k_cd_wg")
+    if desc.get("schedule") == "operator":
+        # k_gs_sweep streams the Gauss-Seidel operator, U x U complex FP64 (k_gs_one keeps it)
+        sweep_kernel = "k_gs_one" if desc["workgroups"] == 1 else "k_gs_sweep"
+        h_bytes = 16.0 * a.U * a.U
     if desc.get("lookahead_panels") == 2:
         sweep_kernel = "k_cd_panel_deep"
     if prec in ("bf16", "fp8"):

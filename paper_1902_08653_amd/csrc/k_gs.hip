@@ -1,0 +1,1015 @@
+// k_gs.hip -- the cyclic sweep of Algorithm 1 on the Gauss-Seidel operator (one instance).
+//
+// For a panel K of k consecutive users let G = H^H H + lambda I, G_KK = D + L + L^H (D the
+// diagonal) and b = H^H (y - H x) - lambda x.  The k sequential updates of the sweep are
+// exactly  delta_K = (D + L)^-1 b_K,  and they change b by -G_JK delta_K in every panel J.
+// With M_K = (D + L)^-1 and W formed once per solve,
+//     W_JK = G_JK M_K (J != K),   W_KK = L^H M_K,
+// a panel step is
+//     b_J <- b_J - W_JK b_K (J != K),   b_K <- -W_KK b_K,   x_K <- x_K + M_K b_K,
+// so the step needs the k values of b_K and nothing of length B: the sweep streams U^2
+// values instead of B U, and one exchange of k values per panel is all that couples the
+// workgroups.  k is 256 instead of the 64 or 128 columns whose tiles of H fit the
+// registers, so a sweep has a quarter of the exchanges.  In exact arithmetic every delta
+// is the sequential sweep's.
+//
+// Everything here runs in FP64, for complex64 input too: G from FP32 sums would lose
+// digits against the residual form of the sweep, and the FP64 vector and matrix rates of
+// gfx950 equal the (unpacked) FP32 vector rate.  So that rounding does not accumulate in b,
+// it is formed anew from H, y and x (two passes over H) after sweeps 2, 8, 40 and 200: the
+// drift of the first, largest steps is gone by then.
+//
+// Stages: k_gs_init, k_gs_gram (64 x 64 blocks of the lower triangle over row splits, on
+// v_mfma_f64_16x16x4_f64), k_gs_assemble (sum of splits, both triangles), k_gs_inv64 and
+// k_gs_mm (the inverse of each D + L by halves, then W), and per segment of sweeps
+// k_gs_rows (r = y - H x), k_gs_grad (b) and the sweep kernel.
+#include "gs.hpp"
+#include "la_common.hpp"
+
+namespace cdm {
+
+namespace {
+
+typedef double acc4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ acc4 mma64(double a, double b, acc4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+template <typename V> __device__ __forceinline__ double2 to_d(V v) {
+    return make_double2((double)v.x, (double)v.y);
+}
+
+// ---- 64 x 64 complex product tiles on the FP64 matrix cores ------------------------------
+// LDS planes with 32 values of the contraction index per row, contiguous (the pitch of 34
+// keeps fragment reads, 16 rows x 2 values per half-wave, off each other's banks).  Four
+// waves, a quadrant of NB x NB 16 x 16 tiles each: 64 x 64 (NB = 2) for the long Gram
+// sums, 32 x 32 (NB = 1) for the products around the inverse, which have few tiles.
+constexpr int MP = 34, MK = 32;
+template <int NB> struct MmAcc {
+    acc4 r[NB][NB], i[NB][NB];
+    __device__ void zero() {
+#pragma unroll
+        for (int a = 0; a < NB; ++a)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                r[a][b] = acc4{0.0, 0.0, 0.0, 0.0};
+                i[a][b] = acc4{0.0, 0.0, 0.0, 0.0};
+            }
+    }
+    // += op(A) B over the staged 32 values; CONJ: op(A) = conj(A)
+    template <bool CONJ> __device__ void step(const double* ar_, const double* ai_, const double* br_,
+                                              const double* bi_, int lane, int wv) {
+        const int qi = wv >> 1, qj = wv & 1;
+#pragma unroll 4
+        for (int k0 = 0; k0 < MK; k0 += 4) {
+            const int rk = k0 + (lane >> 4);
+            double ar[NB], ai[NB], br[NB], bi[NB];
+#pragma unroll
+            for (int a = 0; a < NB; ++a) {
+                const int ra = (16 * NB * qi + 16 * a + (lane & 15)) * MP + rk;
+                const int rb = (16 * NB * qj + 16 * a + (lane & 15)) * MP + rk;
+                ar[a] = ar_[ra];
+                ai[a] = CONJ ? -ai_[ra] : ai_[ra];
+                br[a] = br_[rb];
+                bi[a] = bi_[rb];
+            }
+            // the two products of an accumulator are kept apart: back to back the second waits
+#pragma unroll
+            for (int a = 0; a < NB; ++a)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    r[a][b] = mma64(ar[a], br[b], r[a][b]);
+                    i[a][b] = mma64(ar[a], bi[b], i[a][b]);
+                }
+#pragma unroll
+            for (int a = 0; a < NB; ++a)
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    r[a][b] = mma64(-ai[a], bi[b], r[a][b]);
+                    i[a][b] = mma64(ai[a], br[b], i[a][b]);
+                }
+        }
+    }
+    // f(row, col, value) for this lane's values of the tile
+    template <class F> __device__ void each(int lane, int wv, F f) const {
+#pragma unroll
+        for (int a = 0; a < NB; ++a)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    f(16 * NB * (wv >> 1) + 16 * a + (lane >> 4) + 4 * e, 16 * NB * (wv & 1) + 16 * b + (lane & 15),
+                      make_double2(r[a][b][e], i[a][b][e]));
+    }
+};
+
+__device__ __forceinline__ void lower_block(int n, int& bi, int& bj) {   // n -> (bi, bj), bi >= bj, row by row
+    bi = (int)((sqrtf(8.f * (float)n + 1.f) - 1.f) * 0.5f);
+    while ((bi + 1) * (bi + 2) / 2 <= n) ++bi;
+    while (bi * (bi + 1) / 2 > n) --bi;
+    bj = n - bi * (bi + 1) / 2;
+}
+
+}  // namespace
+
+// r = y, x = x0 or 0 (FP64, zero past U), and the control and exchange words cleared
+template <typename T>
+__global__ __launch_bounds__(256) void k_gs_init(const cv<T>* __restrict__ y, const cv<T>* __restrict__ x0, int B,
+                                                 int U, int Up, double2* __restrict__ r, double2* __restrict__ x,
+                                                 uint64_t* __restrict__ clear, int nclear) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < B) r[i] = to_d(y[i]);
+    if (i < Up) x[i] = (x0 && i < U) ? to_d(x0[i]) : make_double2(0.0, 0.0);
+    for (int k = i; k < nclear; k += gridDim.x * 256) clear[k] = 0;
+}
+
+// One 64 x 64 block (bi, bj) of the lower triangle of H^H H over one split of the rows.
+template <typename T>
+__global__ __launch_bounds__(256) void k_gs_gram(const cv<T>* __restrict__ H, int64_t ld, int B, int U,
+                                                 int rows_per_split, double2* __restrict__ gpart, int nblk) {
+    __shared__ double tile[4][64 * MP];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    int bi, bj;
+    lower_block(blockIdx.x, bi, bj);
+    const int r_lo = blockIdx.y * rows_per_split, r_hi = min(B, r_lo + rows_per_split);
+    const bool same = bi == bj;
+    auto fetch = [&](cv<T>(&v)[8], int c0, int r0) {
+        const int row = r0 + (tid & 31);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int col = c0 + (tid >> 5) + 8 * k;
+            v[k] = (row < r_hi && col < U) ? H[(int64_t)col * ld + row] : czero<T>();
+        }
+    };
+    auto put = [&](const cv<T>(&v)[8], double* tr, double* ti) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int o = ((tid >> 5) + 8 * k) * MP + (tid & 31);
+            tr[o] = v[k].x;
+            ti[o] = v[k].y;
+        }
+    };
+    MmAcc<2> acc;
+    acc.zero();
+    cv<T> va[8], vb[8];
+    if (r_lo < r_hi) {
+        fetch(va, bi * 64, r_lo);
+        if (!same) fetch(vb, bj * 64, r_lo);
+    }
+    for (int r0 = r_lo; r0 < r_hi; r0 += MK) {
+        put(va, tile[0], tile[1]);
+        if (!same) put(vb, tile[2], tile[3]);
+        __syncthreads();
+        if (r0 + MK < r_hi) {   // in flight during this step's products
+            fetch(va, bi * 64, r0 + MK);
+            if (!same) fetch(vb, bj * 64, r0 + MK);
+        }
+        acc.template step<true>(tile[0], tile[1], same ? tile[0] : tile[2], same ? tile[1] : tile[3], lane, wv);
+        __syncthreads();
+    }
+    double2* out = gpart + ((int64_t)blockIdx.y * nblk + blockIdx.x) * 4096;
+    acc.each(lane, wv, [&](int u, int v, double2 z) { out[u * 64 + v] = z; });
+}
+
+// A (Up x Up, row-major) = the sum of the splits in a fixed order, both triangles (the
+// upper as the conjugate of the lower), zero past U.  A workgroup takes 16 rows of a block,
+// a thread four of their elements with the loads of four splits in flight.
+__global__ __launch_bounds__(256) void k_gs_assemble(const double2* __restrict__ gpart, int nsplit, int nblk, int Up,
+                                                     double2* __restrict__ A) {
+    __shared__ double2 t[16][65];
+    int bi, bj;
+    lower_block(blockIdx.x, bi, bj);
+    const int i0 = 16 * blockIdx.y;
+    double2 s[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) s[m] = make_double2(0.0, 0.0);
+    if ((int)blockIdx.x < nblk) {   // blocks past the last one that holds users are zero
+        const double2* p = gpart + (int64_t)blockIdx.x * 4096 + i0 * 64 + threadIdx.x;
+        const int64_t step = (int64_t)nblk * 4096;
+        int k = 0;
+        for (; k + 3 < nsplit; k += 4) {
+            double2 v[4][4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) v[q][m] = p[(k + q) * step + 256 * m];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    s[m].x += v[q][m].x;
+                    s[m].y += v[q][m].y;
+                }
+        }
+        for (; k < nsplit; ++k) {
+            double2 v[4];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) v[m] = p[k * step + 256 * m];
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                s[m].x += v[m].x;
+                s[m].y += v[m].y;
+            }
+        }
+    }
+    const int j = threadIdx.x & 63;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int i = (threadIdx.x >> 6) + 4 * m;
+        t[i][j] = s[m];
+        // a diagonal block's own upper triangle comes from its lower one
+        if (bi != bj || j <= i0 + i) A[(int64_t)(bi * 64 + i0 + i) * Up + bj * 64 + j] = s[m];
+    }
+    __syncthreads();
+    const int i = threadIdx.x & 15;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int c = (threadIdx.x >> 4) + 16 * m;
+        const double2 v = t[i][c];
+        if (bi != bj || c < i0 + i) A[(int64_t)(bj * 64 + c) * Up + bi * 64 + i0 + i] = make_double2(v.x, -v.y);
+    }
+}
+
+// The inverse of one 64 x 64 diagonal block of D + L, into M (panels of k x k, row-major),
+// with the zeros right of it.  Bound by latency (a few workgroups): the four 16 x 16
+// diagonal blocks by substitution, a wave each and a lane per column, then the blocks below
+// them a diagonal at a time, X_ij = -X_ii sum_k L_ik X_kj, on the matrix cores.
+// Inactive coordinates (||h_u||^2 + lambda == 0) get zero rows.
+constexpr int IP = 66;   // pitch of the LDS planes
+constexpr size_t GS_INV_LDS = (size_t)4 * 64 * IP * 8;
+__global__ __launch_bounds__(256) void k_gs_inv64(const double2* __restrict__ A, int Up, int U, int k, double lambda,
+                                                  double2* __restrict__ M, uint32_t* __restrict__ status) {
+    extern __shared__ __attribute__((aligned(16))) double inv_s[];
+    double* Lr = inv_s;
+    double* Li = Lr + 64 * IP;
+    double* Xr = Li + 64 * IP;
+    double* Xi = Xr + 64 * IP;
+    __shared__ double rd[64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int u0 = blockIdx.x * 64;
+    double2 av[16];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) av[m] = A[(int64_t)(u0 + (tid >> 6) + 4 * m) * Up + u0 + (tid & 63)];
+#pragma unroll
+    for (int m = 0; m < 16; ++m) {
+        const int i = (tid >> 6) + 4 * m, j = tid & 63;
+        const double2 v = av[m];
+        Lr[i * IP + j] = j < i ? v.x : 0.0;
+        Li[i * IP + j] = j < i ? v.y : 0.0;
+        Xr[i * IP + j] = 0.0;
+        Xi[i * IP + j] = 0.0;
+        if (i == j) {
+            const double d = v.x + lambda;
+            const bool live = u0 + i < U && d > 0.0;
+            if (u0 + i < U && !live) {
+                // a NaN energy is not an inactive coordinate: it goes on as NaN
+                if (d == d) atomicOr(status, (uint32_t)CDM_INFO_ZERO_COLUMN);
+                rd[i] = d == d ? 0.0 : d;
+            } else {
+                rd[i] = live ? 1.0 / d : 0.0;
+            }
+        }
+    }
+    __syncthreads();
+    if (lane < 16) {
+        const int o = 16 * wv;
+        double xr[16], xi[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            double sr = i == lane ? 1.0 : 0.0, si = 0.0;
+#pragma unroll
+            for (int q = 0; q < i; ++q) {
+                const double lr = Lr[(o + i) * IP + o + q], li = Li[(o + i) * IP + o + q];
+                sr -= lr * xr[q] - li * xi[q];
+                si -= lr * xi[q] + li * xr[q];
+            }
+            const double d = rd[o + i];
+            xr[i] = i >= lane ? sr * d : 0.0;
+            xi[i] = i >= lane ? si * d : 0.0;
+            Xr[(o + i) * IP + o + lane] = xr[i];
+            Xi[(o + i) * IP + o + lane] = xi[i];
+        }
+    }
+    __syncthreads();
+    const int lr_ = lane & 15, lk = lane >> 4;
+    for (int dg = 1; dg < 4; ++dg) {
+        if (wv < 4 - dg) {
+            const int bi = wv + dg, bj = wv;
+            acc4 cr = {0, 0, 0, 0}, ci = {0, 0, 0, 0};
+            for (int q = 16 * bj; q < 16 * bi; q += 4) {
+                const double ar = Lr[(16 * bi + lr_) * IP + q + lk], ai = Li[(16 * bi + lr_) * IP + q + lk];
+                const double br = Xr[(q + lk) * IP + 16 * bj + lr_], bm = Xi[(q + lk) * IP + 16 * bj + lr_];
+                cr = mma64(ar, br, cr);
+                cr = mma64(-ai, bm, cr);
+                ci = mma64(ar, bm, ci);
+                ci = mma64(ai, br, ci);
+            }
+            // the sum goes through this block's own place in X to become an operand
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                Xr[(16 * bi + lk + 4 * e) * IP + 16 * bj + lr_] = cr[e];
+                Xi[(16 * bi + lk + 4 * e) * IP + 16 * bj + lr_] = ci[e];
+            }
+            __builtin_amdgcn_wave_barrier();
+            acc4 dr = {0, 0, 0, 0}, di = {0, 0, 0, 0};
+#pragma unroll
+            for (int q = 0; q < 16; q += 4) {
+                const double ar = -Xr[(16 * bi + lr_) * IP + 16 * bi + q + lk];
+                const double ai = -Xi[(16 * bi + lr_) * IP + 16 * bi + q + lk];
+                const double br = Xr[(16 * bi + q + lk) * IP + 16 * bj + lr_];
+                const double bm = Xi[(16 * bi + q + lk) * IP + 16 * bj + lr_];
+                dr = mma64(ar, br, dr);
+                dr = mma64(-ai, bm, dr);
+                di = mma64(ar, bm, di);
+                di = mma64(ai, br, di);
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                Xr[(16 * bi + lk + 4 * e) * IP + 16 * bj + lr_] = dr[e];
+                Xi[(16 * bi + lk + 4 * e) * IP + 16 * bj + lr_] = di[e];
+            }
+        }
+        __syncthreads();
+    }
+    const int K = u0 / k, c0 = u0 % k;
+    double2* Mk = M + (int64_t)K * k * k + (int64_t)c0 * k;
+    for (int e = tid; e < 4096; e += 256)
+        Mk[(int64_t)(e >> 6) * k + c0 + (e & 63)] =
+            make_double2(Xr[(e >> 6) * IP + (e & 63)], Xi[(e >> 6) * IP + (e & 63)]);
+    const int rest = k - c0 - 64;
+    for (int e = tid; e < 64 * rest; e += 256)
+        Mk[(int64_t)(e / rest) * k + c0 + 64 + e % rest] = make_double2(0.0, 0.0);
+}
+
+// 32 x 32 tiles of the products around the inverse:
+//   MERGE_T  T21 = L21 X11, MERGE_X  X21 = -X22 T21: the lower-left half of a 2s x 2s
+//            inverse from its two s x s halves (T in W's space, which is not yet in use);
+//   FOLD     W_JK = G_JK M_K, for J in K's panel L^H M_K (strictly upper triangle of G_KK);
+//   FOLD_V   V = -M L^H for a single panel (the iteration on delta itself).
+enum { MM_MERGE_T = 0, MM_MERGE_X = 1, MM_FOLD = 2, MM_FOLD_V = 3 };
+template <int MODE>
+__global__ __launch_bounds__(256) void k_gs_mm(const double2* __restrict__ A, double2* __restrict__ M,
+                                               double2* __restrict__ W, int Up, int k, int s) {
+    __shared__ double tile[4][32 * MP];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int kb = k / 32;
+    const int64_t kk = (int64_t)k * k;
+    const double2 *a, *b;
+    double2* c;
+    int64_t lda, ldb, ldc;
+    int c_lo, c_hi, tri = -1;        // tri: the chunk whose diagonal tile counts strictly above the diagonal only
+    double sign = 1.0;
+    if (MODE == MM_MERGE_T || MODE == MM_MERGE_X) {
+        const int sb = s / 32;
+        int n = blockIdx.x;
+        const int j = n % sb;
+        n /= sb;
+        const int i = n % sb;
+        n /= sb;
+        const int q = n % (kb / (2 * sb)), p = n / (kb / (2 * sb));
+        const int lo = 2 * q * s, hi = lo + s;
+        const int64_t pm = p * kk;
+        if (MODE == MM_MERGE_T) {
+            a = A + (int64_t)(p * k + hi + 32 * i) * Up + p * k + lo;
+            lda = Up;
+            b = M + pm + (int64_t)lo * k + lo + 32 * j;
+            c = W + pm + (int64_t)(hi + 32 * i) * k + lo + 32 * j;
+            c_lo = j;
+            c_hi = sb;
+        } else {
+            a = M + pm + (int64_t)(hi + 32 * i) * k + hi;
+            lda = k;
+            b = W + pm + (int64_t)hi * k + lo + 32 * j;
+            c = M + pm + (int64_t)(hi + 32 * i) * k + lo + 32 * j;
+            c_lo = 0;
+            c_hi = i + 1;
+            sign = -1.0;
+        }
+        ldb = ldc = k;
+    } else if (MODE == MM_FOLD) {
+        const int nb = Up / 32;
+        const int J = blockIdx.x % nb, j = blockIdx.x / nb;   // row block, column block of W
+        const int K = j / kb, jl = j % kb, Jl = J - K * kb;
+        a = A + (int64_t)J * 32 * Up + K * k;
+        lda = Up;
+        b = M + K * kk + 32 * jl;
+        ldb = k;
+        c = W + (int64_t)J * 32 * Up + j * 32;
+        ldc = Up;
+        c_lo = jl;
+        c_hi = kb;
+        if (Jl >= 0 && Jl < kb) {
+            c_lo = max(jl, Jl);
+            tri = Jl;
+        }
+    } else {
+        const int j = blockIdx.x % kb, i = blockIdx.x / kb;
+        a = M + (int64_t)i * 32 * k;
+        lda = k;
+        b = A + 32 * j;
+        ldb = Up;
+        c = W + (int64_t)i * 32 * k + j * 32;
+        ldc = k;
+        c_lo = 0;
+        c_hi = min(i, j) + 1;
+        tri = j;
+        sign = -1.0;
+    }
+    double2 va[4], vb[4];
+    const int i_ = tid >> 5, q_ = tid & 31;
+    auto fetch = [&](int ch) {   // chunk ch: 32 values of the contraction index
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            va[m] = a[(int64_t)(i_ + 8 * m) * lda + 32 * ch + q_];
+            vb[m] = b[(int64_t)(32 * ch + i_ + 8 * m) * ldb + q_];
+        }
+        if ((MODE == MM_FOLD || MODE == MM_FOLD_V) && ch == tri) {
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                if (q_ <= i_ + 8 * m) {
+                    if (MODE == MM_FOLD) va[m] = make_double2(0.0, 0.0);
+                    else vb[m] = make_double2(0.0, 0.0);
+                }
+        }
+    };
+    MmAcc<1> acc;
+    acc.zero();
+    if (c_lo < c_hi) fetch(c_lo);
+    for (int ch = c_lo; ch < c_hi; ++ch) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int oa = (i_ + 8 * m) * MP + q_, ob = q_ * MP + i_ + 8 * m;
+            tile[0][oa] = va[m].x;
+            tile[1][oa] = va[m].y;
+            tile[2][ob] = vb[m].x;
+            tile[3][ob] = vb[m].y;
+        }
+        __syncthreads();
+        if (ch + 1 < c_hi) fetch(ch + 1);
+        acc.template step<false>(tile[0], tile[1], tile[2], tile[3], lane, wv);
+        __syncthreads();
+    }
+    acc.each(lane, wv, [&](int i, int j, double2 z) {
+        c[(int64_t)i * ldc + j] = make_double2(sign * z.x, sign * z.y);
+    });
+}
+
+// r = y - H x: a workgroup takes 16 rows, 16 threads of them a column group each.
+template <typename T>
+__global__ __launch_bounds__(256) void k_gs_rows(const cv<T>* __restrict__ H, int64_t ld, int B, int U,
+                                                 const cv<T>* __restrict__ y, const double2* __restrict__ x,
+                                                 double2* __restrict__ r, const uint32_t* __restrict__ done) {
+    if (*done) return;
+    __shared__ double2 s[16][17];
+    const int i = threadIdx.x & 15, g = threadIdx.x >> 4;
+    const int row = blockIdx.x * 16 + i;
+    const int rc = min(row, B - 1);
+    double2 a0 = make_double2(0.0, 0.0), a1 = a0;
+    int u = g;
+    for (; u + 48 < U; u += 64) {
+        cv<T> h[4];
+        double2 xv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) h[q] = H[(int64_t)(u + 16 * q) * ld + rc];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) xv[q] = x[u + 16 * q];
+        cfma(a0, to_d(h[0]), xv[0]);
+        cfma(a1, to_d(h[1]), xv[1]);
+        cfma(a0, to_d(h[2]), xv[2]);
+        cfma(a1, to_d(h[3]), xv[3]);
+    }
+    for (; u < U; u += 16) cfma(a0, to_d(H[(int64_t)u * ld + rc]), x[u]);
+    s[g][i] = make_double2(a0.x + a1.x, a0.y + a1.y);
+    __syncthreads();
+    if (threadIdx.x < 16 && row < B) {
+        double2 z = to_d(y[row]);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            z.x -= s[q][i].x;
+            z.y -= s[q][i].y;
+        }
+        r[row] = z;
+    }
+}
+
+// b_u = h_u^H r - lambda x_u, a workgroup per user (zero past U)
+template <typename T>
+__global__ __launch_bounds__(256) void k_gs_grad(const cv<T>* __restrict__ H, int64_t ld, int B, int U,
+                                                 const double2* __restrict__ r, const double2* __restrict__ x,
+                                                 double lambda, double2* __restrict__ b,
+                                                 const uint32_t* __restrict__ done) {
+    if (*done) return;
+    __shared__ double2 s[4];
+    const int u = blockIdx.x;
+    double2 a0 = make_double2(0.0, 0.0), a1 = a0;
+    if (u < U) {
+        const cv<T>* h = H + (int64_t)u * ld;
+        int i = threadIdx.x;
+        for (; i + 768 < B; i += 1024) {
+            cv<T> hv[4];
+            double2 rv[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) hv[q] = h[i + 256 * q];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) rv[q] = r[i + 256 * q];
+            cfma_conj(a0, to_d(hv[0]), rv[0]);
+            cfma_conj(a1, to_d(hv[1]), rv[1]);
+            cfma_conj(a0, to_d(hv[2]), rv[2]);
+            cfma_conj(a1, to_d(hv[3]), rv[3]);
+        }
+        for (; i < B; i += 256) cfma_conj(a0, to_d(h[i]), r[i]);
+    }
+    a0.x = group_sum<1>(a0.x + a1.x);
+    a0.y = group_sum<1>(a0.y + a1.y);
+    if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = a0;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const double2 xv = x[u];
+        b[u] = make_double2((s[0].x + s[1].x) + (s[2].x + s[3].x) - lambda * xv.x,
+                            (s[0].y + s[1].y) + (s[2].y + s[3].y) - lambda * xv.y);
+    }
+}
+
+__device__ __forceinline__ void gs_info(cdm_info* info, int sweeps, double S, double X, double tol, bool ok) {
+    const double rel = X > 0.0 ? sqrt(S / X) : (S > 0.0 ? INFINITY : 0.0);
+    int fl = 0;
+    if (tol > 0.0 && !(rel <= tol)) fl |= CDM_INFO_NOT_CONVERGED;
+    if (!ok) fl |= CDM_INFO_TIMEOUT;
+    cdm_info o;
+    o.sweeps = sweeps;
+    o.flags = fl;
+    o.rel_step = rel;
+    o.resid = -1.0;
+    o.reserved = 0.0;
+    *info = o;
+}
+
+// Sweeps t0 + 1 .. t1 of a single panel of at most 128 users, in one workgroup: with one
+// panel the deltas follow each other by delta <- V delta, V = -M L^H, so V stays in
+// registers (128 x 128 complex FP64 = 64 VGPRs of 1024 threads) and a sweep is one product
+// and two barriers.  Thread: row group of 2 rows x 8 columns (16 lanes to a row pair).
+__global__ __launch_bounds__(1024) void k_gs_one(const double2* __restrict__ V, const double2* __restrict__ M,
+                                                 const double2* __restrict__ b, double2* __restrict__ x, int U,
+                                                 int t0, int t1, double tol, uint32_t* __restrict__ done,
+                                                 cdm_info* __restrict__ info) {
+    if (*done) return;
+    __shared__ double2 ds[2][128];
+    __shared__ double2 st[2][16];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int cl = lane & 15, r0 = wv * 8 + (lane >> 4) * 2;
+    double2 w[2][8], xv[2], d[2];
+    // delta of sweep t0 + 1 is M b
+    if (tid < 128) ds[1][tid] = b[tid];
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) w[p][q] = M[(r0 + p) * 128 + cl + 16 * q];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) xv[p] = x[r0 + p];
+    __syncthreads();
+    auto product = [&](const double2* in) __attribute__((always_inline)) {
+        d[0] = d[1] = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const double2 v = in[cl + 16 * q];
+            cfma(d[0], w[0][q], v);
+            cfma(d[1], w[1][q], v);
+        }
+    };
+    product(ds[1]);
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) w[p][q] = V[(r0 + p) * 128 + cl + 16 * q];
+    int t = t0;
+    double S = 0.0, X = 0.0;
+    bool stop = false;
+    while (t < t1 && !stop) {
+        double2* out = ds[(t - t0) & 1];
+        if (t > t0) product(ds[(t - t0 + 1) & 1]);
+        double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            d[p].x += row_ror<1>(d[p].x);
+            d[p].y += row_ror<1>(d[p].y);
+            d[p].x += row_ror<2>(d[p].x);
+            d[p].y += row_ror<2>(d[p].y);
+            d[p].x += row_ror<4>(d[p].x);
+            d[p].y += row_ror<4>(d[p].y);
+            d[p].x += row_ror<8>(d[p].x);
+            d[p].y += row_ror<8>(d[p].y);
+            xv[p].x += d[p].x;
+            xv[p].y += d[p].y;
+            if (cl == 0) out[r0 + p] = d[p];
+            s1 += cabs2d(d[p]);
+            s2 += cabs2d(xv[p]);
+        }
+        s1 = swap_add<32>(swap_add<16>(s1));   // over the wave's four row pairs
+        s2 = swap_add<32>(swap_add<16>(s2));
+        if (lane == 0) st[t & 1][wv] = make_double2(s1, s2);
+        __syncthreads();
+        ++t;
+        if (tol > 0.0 || t == t1) {   // the 16 waves' parts: a lane each, summed over the row of 16
+            const double2 v = st[(t - 1) & 1][cl];
+            S = v.x;
+            X = v.y;
+            S += row_ror<1>(S);
+            X += row_ror<1>(X);
+            S += row_ror<2>(S);
+            X += row_ror<2>(X);
+            S += row_ror<4>(S);
+            X += row_ror<4>(X);
+            S += row_ror<8>(S);
+            X += row_ror<8>(X);
+            // the two roots only where they can decide: FP64 roots cost as much as the product
+            stop = tol > 0.0 && !(S > 2.0 * tol * tol * X) && sqrt(S) <= tol * sqrt(X);
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+        if (cl == 0) x[r0 + p] = xv[p];
+    if (tid == 0) {
+        gs_info(info, t, S, X, tol, true);
+        if (stop) *done = 1;
+    }
+}
+
+// Sweeps t0 + 1 .. t1 over several workgroups (cooperative launch).  Workgroup w owns R
+// consecutive rows of W, b and x (all in one panel); its NW tile waves take RW = R / NW
+// rows each, a lane per column modulo 64, the row's values of b and x in every lane.  The
+// CW other waves do every exchange: per step they gather the k values of b_K (tagged
+// words, one memory round trip, no flag) into LDS behind one barrier.  Each tile wave
+// loads its tile of the next step once it is done with this one, so the stream of W
+// (U^2 x 16 B per sweep, from L2 or MALL) runs during the exchange.
+// Slots: b_K of sweep t in slot t & 1 of panel K.  To publish b_K of sweep t + 2 a
+// workgroup has gathered every panel of sweep t + 1, and its owners published that after
+// they had gathered b_K of sweep t, so the slot is free.
+// Stop: the owners of a panel know the deltas, so each workgroup publishes its part of
+// (sum |delta|^2, sum |x|^2) of a sweep; every workgroup adds all parts in the same order
+// two sweeps later, at its own panel, and stops with the x of that sweep (the one before
+// its current x): the exchange of the statistics is hardly ever waited for.  The
+// workgroups that stop have published all that the others need to reach their own panel.
+constexpr int GS_CW = 4;
+// value i of n in an exchange slot: three planes of n tagged words, so that a wave's loads
+// of one word are contiguous
+__device__ __forceinline__ void gs_put(uint64_t* p, int n, int i, double2 v, uint32_t tag) {
+    const uint64_t a = (uint64_t)__double_as_longlong(v.x), b = (uint64_t)__double_as_longlong(v.y);
+    Tagged<double>::st48(p + i, a, tag);
+    Tagged<double>::st48(p + n + i, (a >> 48) | (b << 16), tag);
+    Tagged<double>::st48(p + 2 * n + i, b >> 32, tag);
+}
+__device__ __forceinline__ bool gs_get(const uint64_t* p, int n, int i, uint32_t tag, double2& v) {
+    const uint64_t w0 = ld_tag(p + i), w1 = ld_tag(p + n + i), w2 = ld_tag(p + 2 * n + i);
+    const uint64_t t = (uint64_t)(tag & 0xffffu), m = 0xffffffffffffull;
+    v.x = __longlong_as_double((long long)((w0 & m) | ((w1 & 0xffffull) << 48)));
+    v.y = __longlong_as_double((long long)(((w1 & m) >> 16) | ((w2 & 0xffffffffull) << 32)));
+    return ((w0 >> 48) == t) & ((w1 >> 48) == t) & ((w2 >> 48) == t);
+}
+
+template <int R, int NW, int KC>
+__global__ __launch_bounds__(64 * (NW + GS_CW), 1) void k_gs_sweep(GsSweepArgs a, int t0, int t1) {
+    constexpr int RW = R / NW, k = 64 * KC, GC = KC / GS_CW;
+    if (*a.done) return;
+    __shared__ double2 bs[2][k];
+    __shared__ double2 sacc[2][NW];
+    __shared__ int go[2][GS_CW];
+    extern __shared__ __attribute__((aligned(16))) double2 ms[];   // this workgroup's rows of M: R x k
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int w = blockIdx.x, P = gridDim.x, npan = a.npan, Up = a.Up;
+    const int Kw = w * R / k;               // the panel that holds this workgroup's rows
+    const bool comm = wid >= NW, lead = wid == NW;
+    const int row0 = w * R + (comm ? 0 : wid * RW);
+    double2 b[RW], x[RW], xp[RW], tile[RW][KC];
+    uint64_t* const xch = a.xch;            // [npan][2] slots of k values
+    uint64_t* const sch = a.xch + (int64_t)npan * 2 * k * 3;   // [4] slots of P values
+    auto publish = [&](int t) __attribute__((always_inline)) {   // this wave's rows of b for sweep t
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+            if (lane == r) gs_put(xch + (int64_t)(Kw * 2 + (t & 1)) * k * 3, k, (row0 + r) % k, b[r], (uint32_t)t);
+    };
+    auto load = [&](int K) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int q = 0; q < KC; ++q) tile[r][q] = a.W[(int64_t)(row0 + r) * Up + K * k + lane + 64 * q];
+    };
+    if (!comm) {
+#pragma unroll
+        for (int r = 0; r < RW; ++r) b[r] = a.b[row0 + r];
+        if (Kw == 0) publish(t0 + 1);
+        load(0);
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            x[r] = xp[r] = a.x[row0 + r];
+#pragma unroll
+            for (int q = 0; q < KC; ++q)
+                ms[(wid * RW + r) * k + lane + 64 * q] =
+                    a.M[(int64_t)Kw * k * k + (int64_t)((row0 + r) % k) * k + lane + 64 * q];
+        }
+    }
+    double S = 0.0, X = 0.0;
+    uint64_t tw = 0;
+    auto expired = [&]() __attribute__((always_inline)) -> bool {   // bounded waits: true once the wait is given up
+        if (ld_relaxed(a.abort_flag)) return true;
+        const uint64_t now = wall_clock64();
+        if (!tw) tw = now;
+        if (now - tw > a.timeout_ticks) {
+            if (lane == 0) st_relaxed(a.abort_flag, 1u);
+            return true;
+        }
+        return false;
+    };
+    // S, X: the parts of sweep t summed in a fixed order (every lane and workgroup alike)
+    auto stats = [&](int t) __attribute__((always_inline)) -> bool {
+        for (;;) {
+            bool ok = true;
+            S = X = 0.0;
+            for (int p = lane; p < P; p += 64) {
+                double2 v;
+                ok &= gs_get(sch + (int64_t)(t & 3) * P * 3, P, p, (uint32_t)t, v);
+                S += v.x;
+                X += v.y;
+            }
+            if (__all(ok)) break;
+            if (expired()) return false;
+        }
+        S = wave_allsum(S);
+        X = wave_allsum(X);
+        tw = 0;
+        return true;
+    };
+    auto put_stats = [&](int t, int sp) __attribute__((always_inline)) {
+        double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+            s1 += sacc[sp][q].x;
+            s2 += sacc[sp][q].y;
+        }
+        if (lane == 0) gs_put(sch + (int64_t)(t & 3) * P * 3, P, w, make_double2(s1, s2), (uint32_t)t);
+    };
+    auto met = [&]() { return a.tol > 0.0 && !(S > 2.0 * a.tol * a.tol * X) && sqrt(S) <= a.tol * sqrt(X); };
+
+    int code = 1, t = t0 + 1, K = 0, owed = 0, par = 0;   // code: 1 goes on, 2 x of the sweep before, 3 given up
+    for (;; par ^= 1) {
+        if (comm) {
+            int g = 1;
+            const uint64_t* src = xch + (int64_t)(K * 2 + (t & 1)) * k * 3;
+            const int i0 = (wid - NW) * 64 * GC + lane;
+            double2 v[GC];
+            for (;;) {
+                bool ok = true;
+#pragma unroll
+                for (int q = 0; q < GC; ++q) ok &= gs_get(src, k, i0 + 64 * q, (uint32_t)t, v[q]);
+                if (__all(ok)) break;
+                if (expired()) {
+                    g = 3;
+                    break;
+                }
+            }
+            tw = 0;
+#pragma unroll
+            for (int q = 0; q < GC; ++q) bs[par][i0 + 64 * q] = v[q];
+            if (lead && g == 1 && a.tol > 0.0 && K == Kw && t - 2 > t0) {
+                if (!stats(t - 2))
+                    g = 3;
+                else if (met()) {
+                    g = 2;
+                    if (w == 0 && lane == 0) gs_info(a.info, t - 2, S, X, a.tol, true);
+                }
+            }
+            if (lane == 0) go[par][wid - NW] = g;
+        }
+        __syncthreads();
+        code = 1;
+#pragma unroll
+        for (int q = 0; q < GS_CW; ++q) code = max(code, go[par][q]);
+        if (code != 1) break;
+        const bool own = K == Kw;
+        const int Kn = K + 1 < npan ? K + 1 : 0;
+        const bool last = t == t1 && Kn == 0;
+        if (comm) {
+            if (lead && owed) put_stats(owed, par ^ 1);   // written before this barrier
+            owed = own ? t : 0;
+        } else {
+            double2 v[KC];
+#pragma unroll
+            for (int q = 0; q < KC; ++q) v[q] = bs[par][lane + 64 * q];
+#pragma unroll
+            for (int r = 0; r < RW; ++r) {
+                double2 s = make_double2(0.0, 0.0);
+#pragma unroll
+                for (int q = 0; q < KC; ++q) cfma(s, tile[r][q], v[q]);
+                s.x = group_sum<1>(s.x);
+                s.y = group_sum<1>(s.y);
+                b[r].x = own ? -s.x : b[r].x - s.x;
+                b[r].y = own ? -s.y : b[r].y - s.y;
+            }
+            if (Kn == Kw && !last) publish(Kn == 0 ? t + 1 : t);
+            if (npan > 1 && !last) load(Kn);
+            if (own) {
+                double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+                for (int r = 0; r < RW; ++r) {
+                    double2 s = make_double2(0.0, 0.0);
+#pragma unroll
+                    for (int q = 0; q < KC; ++q) cfma(s, ms[(wid * RW + r) * k + lane + 64 * q], v[q]);
+                    s.x = group_sum<1>(s.x);
+                    s.y = group_sum<1>(s.y);
+                    xp[r] = x[r];
+                    x[r].x += s.x;
+                    x[r].y += s.y;
+                    s1 += cabs2d(s);
+                    s2 += cabs2d(x[r]);
+                }
+                if (lane == 0) sacc[par][wid] = make_double2(s1, s2);
+            }
+        }
+        if (last) break;
+        K = Kn;
+        if (Kn == 0) ++t;
+    }
+    if (code == 1) {   // all sweeps run: the decisions of the last two
+        __syncthreads();
+        if (lead) {
+            int g = 1;
+            if (owed) put_stats(owed, par);
+            bool ok = true;
+            if (a.tol > 0.0 && t1 - 1 > t0) {
+                ok = stats(t1 - 1);
+                if (ok && met()) {
+                    g = 2;
+                    if (w == 0 && lane == 0) gs_info(a.info, t1 - 1, S, X, a.tol, true);
+                }
+            }
+            if (ok && g == 1) {
+                ok = stats(t1);
+                if (ok && met()) g = 4;
+                if (ok && w == 0 && lane == 0) gs_info(a.info, t1, S, X, a.tol, true);
+            }
+            if (lane == 0) go[0][0] = ok ? g : 3;
+        }
+        __syncthreads();
+        code = go[0][0];
+    }
+    if (!comm && lane == 0) {
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+            a.x[row0 + r] = make_double2(code == 2 ? xp[r].x : x[r].x, code == 2 ? xp[r].y : x[r].y);
+    }
+    if (w == 0 && lead && lane == 0) {
+        if (code == 3) gs_info(a.info, t - 1, S, X, a.tol, false);
+        if (code != 1) *a.done = 1;
+    }
+}
+
+// x in the caller's type, and the flags that are known now
+template <typename T>
+__global__ __launch_bounds__(1024) void k_gs_finish(const double2* __restrict__ xw, int U, cv<T>* __restrict__ x,
+                                                    const uint32_t* __restrict__ status, cdm_info* __restrict__ info) {
+    __shared__ int bad;
+    if (threadIdx.x == 0) bad = 0;
+    __syncthreads();
+    int mine = 0;
+    for (int u = threadIdx.x; u < U; u += 1024) {
+        const cv<T> v = cmake<T>((T)xw[u].x, (T)xw[u].y);
+        x[u] = v;
+        if (!isfinite(v.x) || !isfinite(v.y)) mine = 1;
+    }
+    if (mine) bad = 1;
+    __syncthreads();
+    if (threadIdx.x == 0) info->flags |= (int)(*status & CDM_INFO_ZERO_COLUMN) | (bad ? CDM_INFO_NONFINITE : 0);
+}
+
+// ---- host side -----------------------------------------------------------------------------
+
+#define GS_TRY(call)                        \
+    do {                                    \
+        const hipError_t e_ = (call);       \
+        if (e_ != hipSuccess) return e_;    \
+    } while (0)
+
+GsShape gs_shape(int B, int U) {
+    GsShape s;
+    s.k = U <= 128 ? 128 : (U <= 256 ? 256 : 512);
+    s.npan = (U + s.k - 1) / s.k;
+    s.Up = s.npan * s.k;
+    s.one = U <= 128;
+    s.R = s.one ? 128 : 16;
+    s.P = s.Up / s.R;
+    s.nblk = ((U + 63) / 64) * ((U + 63) / 64 + 1) / 2;
+    // splits of the rows: fewest rounds of resident workgroups (two per CU) for the work of
+    // a split (about 10 us per 32 rows at the full rate) and its partial block
+    double best = 0.0;
+    s.nsplit = 1;
+    for (int ns = 1; ns <= 32; ++ns) {
+        const int steps = (B + 32 * ns - 1) / (32 * ns);
+        if (ns > 1 && steps < 1) break;
+        const double rounds = (double)((s.nblk * ns + 511) / 512);
+        const double cost = rounds * (steps * 10.0 + 5.0) + (double)s.nblk * ns * 0.045;
+        if (ns == 1 || cost < best) {
+            best = cost;
+            s.nsplit = ns;
+        }
+    }
+    return s;
+}
+
+size_t gs_exchange_words(const GsShape& s) {
+    return 3 * ((size_t)s.npan * 2 * s.k + 4 * (size_t)s.P);
+}
+
+// the sweep kernel of a tiling: its R and k are the kernel's own (NULL: none is built)
+static const void* gs_sweep_fn(const GsShape& s) {
+    if (s.k == 256 && s.R == 16) return (const void*)k_gs_sweep<16, 8, 4>;
+    if (s.k == 512 && s.R == 16) return (const void*)k_gs_sweep<16, 8, 8>;
+    return nullptr;
+}
+
+template <typename T> static hipError_t launch_gs_t(const GsLaunch& L, hipStream_t st) {
+    const GsShape& s = L.s;
+    const cv<T>* H = (const cv<T>*)L.H;
+    const cv<T>* y = (const cv<T>*)L.y;
+    double2* A = (double2*)L.A;
+    double2* M = (double2*)L.M;
+    double2* W = (double2*)L.W;
+    double2* r = (double2*)L.r;
+    double2* b = (double2*)L.b;
+    double2* x = (double2*)L.xw;
+    uint32_t* done = L.ctr + 4;
+    const int nmax = L.B > s.Up ? L.B : s.Up;
+    hipLaunchKernelGGL(k_gs_init<T>, dim3((nmax + 255) / 256), dim3(256), 0, st, y, (const cv<T>*)L.x0, L.B, L.U, s.Up,
+                       r, x, (uint64_t*)L.ctr, (int)(GS_CTR_WORDS / 2 + gs_exchange_words(s)));
+    GS_TRY(hipGetLastError());
+    int rps = (L.B + s.nsplit - 1) / s.nsplit;
+    rps = (rps + MK - 1) / MK * MK;
+    hipLaunchKernelGGL(k_gs_gram<T>, dim3(s.nblk, s.nsplit), dim3(256), 0, st, H, L.ld, L.B, L.U, rps,
+                       (double2*)L.gpart, s.nblk);
+    const int nb = s.Up / 64;
+    hipLaunchKernelGGL(k_gs_assemble, dim3(nb * (nb + 1) / 2, 4), dim3(256), 0, st, (const double2*)L.gpart, s.nsplit,
+                       s.nblk, s.Up, A);
+    hipLaunchKernelGGL(k_gs_inv64, dim3(nb), dim3(256), GS_INV_LDS, st, A, s.Up, L.U, s.k, L.lambda, M, L.ctr + 3);
+    GS_TRY(hipGetLastError());
+    for (int h = 64; h < s.k; h *= 2) {
+        const int blocks = s.npan * (s.k / (2 * h)) * (h / 32) * (h / 32);
+        hipLaunchKernelGGL(k_gs_mm<MM_MERGE_T>, dim3(blocks), dim3(256), 0, st, A, M, W, s.Up, s.k, h);
+        hipLaunchKernelGGL(k_gs_mm<MM_MERGE_X>, dim3(blocks), dim3(256), 0, st, A, M, W, s.Up, s.k, h);
+    }
+    if (s.one)
+        hipLaunchKernelGGL(k_gs_mm<MM_FOLD_V>, dim3(4 * nb * nb), dim3(256), 0, st, A, M, W, s.Up, s.k, 0);
+    else
+        hipLaunchKernelGGL(k_gs_mm<MM_FOLD>, dim3(4 * nb * nb), dim3(256), 0, st, A, M, W, s.Up, s.k, 0);
+    GS_TRY(hipGetLastError());
+    if (L.ev_pre) GS_TRY(hipEventRecord(L.ev_pre, st));
+    auto refresh = [&](bool rows) -> hipError_t {
+        if (rows) {
+            hipLaunchKernelGGL(k_gs_rows<T>, dim3((L.B + 15) / 16), dim3(256), 0, st, H, L.ld, L.B, L.U, y, x, r, done);
+            GS_TRY(hipGetLastError());
+        }
+        hipLaunchKernelGGL(k_gs_grad<T>, dim3(s.Up), dim3(256), 0, st, H, L.ld, L.B, L.U, r, x, L.lambda, b, done);
+        return hipGetLastError();
+    };
+    if (L.ev_init) GS_TRY(hipEventRecord(L.ev_init, st));
+    GsSweepArgs g;
+    g.W = W;
+    g.M = M;
+    g.b = b;
+    g.x = x;
+    g.xch = (uint64_t*)L.ctr + GS_CTR_WORDS / 2;
+    g.abort_flag = L.ctr + 2;
+    g.done = done;
+    g.info = L.info;
+    g.tol = L.tol;
+    g.timeout_ticks = L.timeout_ticks;
+    g.npan = s.npan;
+    g.Up = s.Up;
+    int t0 = 0;
+    for (int seg = 2; t0 < L.T_max; seg = seg == 2 ? 8 : seg * 5) {
+        GS_TRY(refresh(t0 > 0 || L.x0));
+        int t1 = (seg >= 1000 || L.T_max < seg) ? L.T_max : seg;   // 2, 8, 40, 200, then to the end
+        if (s.one) {
+            hipLaunchKernelGGL(k_gs_one, dim3(1), dim3(1024), 0, st, W, M, b, x, L.U, t0, t1, L.tol, done, L.info);
+            GS_TRY(hipGetLastError());
+        } else {
+            void* args[] = {&g, &t0, &t1};
+            GS_TRY(hipLaunchCooperativeKernel(gs_sweep_fn(s), dim3(s.P), dim3(64 * (8 + GS_CW)), args,
+                                              (size_t)16 * s.R * s.k, st));
+        }
+        t0 = t1;
+    }
+    if (L.ev_sweep) GS_TRY(hipEventRecord(L.ev_sweep, st));
+    hipLaunchKernelGGL(k_gs_finish<T>, dim3(1), dim3(1024), 0, st, x, L.U, (cv<T>*)L.x, L.ctr + 3, L.info);
+    return hipGetLastError();
+}
+
+hipError_t gs_setup(const GsShape& s) {
+    if (!s.one && (!gs_sweep_fn(s) || s.P * s.R != s.Up || s.k % s.R != 0)) return hipErrorInvalidValue;
+    if (!s.one && 16 * s.R * s.k > 48 * 1024)
+        GS_TRY(hipFuncSetAttribute(gs_sweep_fn(s), hipFuncAttributeMaxDynamicSharedMemorySize, 16 * s.R * s.k));
+    return hipFuncSetAttribute((const void*)k_gs_inv64, hipFuncAttributeMaxDynamicSharedMemorySize, (int)GS_INV_LDS);
+}
+
+hipError_t launch_gs(const GsLaunch& L, hipStream_t st) {
+    return L.c128 ? launch_gs_t<double>(L, st) : launch_gs_t<float>(L, st);
+}
+
+}  // namespace cdm

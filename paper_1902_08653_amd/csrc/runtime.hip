@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "cdm.h"
+#include "gs.hpp"
 #include "launch.hpp"
 
 using namespace cdm;
@@ -41,6 +42,7 @@ constexpr double kWgMixedTauC64 = 1e-5;   // inner stop ||delta|| <= tau ||d||: 
 constexpr double kWgMixedTauBf16 = 3e-2;  // BF16 copy (its rounding bounds the outer gain per step)
 constexpr int kCtrWords = 2048;       // control words: counters, abort/status, arrival flags
 constexpr size_t kLdsMax = 160 * 1024;
+constexpr int kGsMaxUsers = 2048;     // operator engine: W (U x U complex FP64, 64 MiB) stays in the MALL
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -119,6 +121,14 @@ struct cdm_plan {
     void* mx_d32 = nullptr;
     void* mx_r32 = nullptr;
     uint32_t* mx_done = nullptr;
+    // Gauss-Seidel operator engine (k_gs.hip)
+    bool gs = false;
+    GsShape gshape;
+    void* gs_A = nullptr;
+    void* gs_W = nullptr;
+    void* gs_r = nullptr;
+    void* gs_b = nullptr;
+    void* gs_x = nullptr;
     // sparse (CSR input)
     int32_t* sp_colptr = nullptr;
     int32_t* sp_fill = nullptr;
@@ -225,6 +235,121 @@ static int32_t setup_wg(cdm_plan* p, int m_max, int n_max, int njobs, int nt) {
 }
 
 extern "C" int32_t cdm_destroy(cdm_plan* p);
+
+// One instance on the Gauss-Seidel operator (k_gs.hip) instead of the panel engine or one
+// workgroup.  Its pre-pass forms H^H H, 4 B U^2 multiply-adds that the others do not spend
+// (B U^2 / 1.5e7 us); its sweep then costs 4 us per 512 users, against 4-6 us per 64
+// (look-ahead) or 9-13 us per 128 (two-hop) and 0.5-0.8 us per user in one workgroup.
+// Measured, old / new in us:
+//   complex128 16000 x 2048:  8 sweeps 2396 / 4914, 16 4056 / 5284, 32 7364 / 5576
+//   complex128  7500 x 1500:  4 sweeps 1080 / 1496,  8 1660 / 1540, 32 5190 / 1905
+//   complex64   4096 x 2048:  8 sweeps 1291 / 1658, 16 2254 / 1850
+//   complex128  3000 x 1000:  4 sweeps 1133 /  468, 32 4466 /  715
+//   complex128   256 x   16:  4 sweeps   56 /   67,  8  103 /   73
+//   complex64    256 x   16:  8 sweeps   73 /   71, 16  134 /   94
+// so the lines are B U <= 1.4e6 (complex128) or 0.8e6 (complex64) per sweep, and 128 or 160
+// column updates in all.  With a tolerance the sweeps are not known; 16 (1e-11) or 10 (1e-6)
+// are what well conditioned channels take.  Past one panel of 128 users the sweep is a
+// cooperative launch, which small instances on one workgroup do not use today.
+static bool gs_applies(const cdm_desc& d, int engine, bool mixed) {
+    if (d.engine != CDM_ENGINE_AUTO || d.C != 1 || d.problem != CDM_UPLINK_LMMSE || d.layout != CDM_DENSE || mixed ||
+        d.panel != 0 || (d.flags & (CDM_F_NO_LOOKAHEAD | CDM_F_DEEP_LOOKAHEAD)) || d.U > kGsMaxUsers)
+        return false;
+    if (engine == CDM_ENGINE_WG && d.U > 128) return false;
+    const bool c128 = d.precision == CDM_C128;
+    const int sweeps = d.tol > 0.0 ? std::min(d.T_max, c128 ? 16 : 10) : d.T_max;
+    return sweeps >= 4 && (int64_t)sweeps * d.U >= (c128 ? 128 : 160) &&
+           (double)d.B * d.U <= sweeps * (c128 ? 1.4e6 : 0.8e6);
+}
+
+static int32_t create_gs(cdm_plan* p, cdm_plan** plan) {
+    const cdm_desc& d = p->d;
+    p->gs = true;
+    p->gshape = gs_shape(d.B, d.U);
+    const GsShape& s = p->gshape;
+    if (s.P > p->ncu || gs_setup(s) != hipSuccess) {
+        delete p;
+        return CDM_ESHAPE;
+    }
+    const size_t sq = 16 * (size_t)s.Up * s.Up;
+    Arena ar;
+    const size_t o_ctr = ar.take(4 * GS_CTR_WORDS + 8 * gs_exchange_words(s));
+    const size_t o_gpart = ar.take((size_t)s.nsplit * s.nblk * 65536);
+    const size_t o_A = ar.take(sq);
+    const size_t o_W = ar.take(sq);
+    const size_t o_M = ar.take(16 * (size_t)s.npan * s.k * s.k);
+    const size_t o_r = ar.take(16 * (size_t)d.B);
+    const size_t o_b = ar.take(16 * (size_t)s.Up);
+    const size_t o_x = ar.take(16 * (size_t)s.Up);
+    const size_t o_res_rpart = ar.take(16 * (size_t)p->nchunk * d.B);
+    const size_t o_res_r = ar.take(16 * (size_t)d.B);
+    const size_t o_res_col = ar.take(16 * (size_t)((d.U + 3) / 4 + 1));
+    const size_t o_res_out = ar.take(8);
+    int32_t st = alloc_ws(p, ar.off);
+    if (st) {
+        delete p;
+        return st;
+    }
+    char* b = p->ws;
+    p->ctr = (uint32_t*)(b + o_ctr);
+    p->gpart = b + o_gpart;
+    p->gs_A = b + o_A;
+    p->gs_W = b + o_W;
+    p->M = b + o_M;
+    p->gs_r = b + o_r;
+    p->gs_b = b + o_b;
+    p->gs_x = b + o_x;
+    p->res_rpart = (double*)(b + o_res_rpart);
+    p->res_r = (double*)(b + o_res_r);
+    p->res_col = (double*)(b + o_res_col);
+    p->res_out = (double*)(b + o_res_out);
+    char buf[512];
+    snprintf(buf, sizeof(buf),
+             "{\"engine\": \"panel\", \"schedule\": \"operator\", \"lookahead_panels\": 0, \"precision\": \"%s\", "
+             "\"B\": %d, \"U\": %d, \"panel\": %d, \"rpl\": %d, \"workgroups\": %d, \"npanels\": %d, "
+             "\"gram_splits\": %d, \"inner_sweeps\": 0, \"workspace\": %zu}",
+             p->c128 ? "c128" : "c64", d.B, d.U, s.k, s.R, s.one ? 1 : s.P, s.npan, s.nsplit, p->ws_bytes);
+    p->text = buf;
+    st = setup_timing(p);
+    if (st) {
+        cdm_destroy(p);
+        return st;
+    }
+    *plan = p;
+    return CDM_OK;
+}
+
+static int32_t solve_gs(cdm_plan* p, const void* H, int64_t ldh, const void* y, double lambda, const void* x0,
+                        void* x, cdm_info* info, hipStream_t st) {
+    GsLaunch L;
+    L.c128 = p->c128;
+    L.s = p->gshape;
+    L.B = p->d.B;
+    L.U = p->d.U;
+    L.H = H;
+    L.ld = ldh;
+    L.y = y;
+    L.x0 = x0;
+    L.x = x;
+    L.info = info;
+    L.lambda = lambda;
+    L.tol = p->d.tol;
+    L.T_max = p->d.T_max;
+    L.timeout_ticks = p->timeout_ticks;
+    L.ctr = p->ctr;
+    L.gpart = p->gpart;
+    L.A = p->gs_A;
+    L.W = p->gs_W;
+    L.M = p->M;
+    L.r = p->gs_r;
+    L.b = p->gs_b;
+    L.xw = p->gs_x;
+    L.ev_pre = p->timed ? p->ev[1] : nullptr;
+    L.ev_init = p->timed ? p->ev[2] : nullptr;
+    L.ev_sweep = p->timed ? p->ev[3] : nullptr;
+    HIP_TRY(launch_gs(L, st));
+    return CDM_OK;
+}
 
 static constexpr int kSpKp = 64;
 
@@ -568,12 +693,13 @@ int32_t cdm_create(const cdm_desc* desc, cdm_plan** plan) {
         return CDM_ESHAPE;
     }
     p->engine = engine;
+    p->nchunk = std::max(1, std::min(64, (d.U + 127) / 128));
+    if (gs_applies(d, engine, mixed)) return create_gs(p, plan);
 
     Arena ar;
     const size_t o_ctr = ar.take(kCtrWords * 4);
     size_t o_jobs = 0, o_r0 = 0, o_M = 0, o_gpart = 0, o_part = 0, o_gbuf = 0, o_e = 0, o_xloc = 0,
            o_msum = 0, o_rpart = 0, o_X = 0, o_X2 = 0;
-    p->nchunk = std::max(1, std::min(64, (d.U + 127) / 128));
     if (engine == CDM_ENGINE_WG) {
         st = setup_wg(p, Bc, d.U, d.C, wg_nt_single(Bc, p->c128));
         if (st) {
@@ -839,8 +965,11 @@ int32_t cdm_solve(cdm_plan* p, const void* H, int64_t ldh, const int32_t* rowptr
 
     if (p->mixed) return solve_mixed(p, H, ldh, rhs, lambda, x0, x, inf, st);
     ev_record(p, 0, st);
-    HIP_TRY(launch_zero_u32(p->ctr, p->engine == CDM_ENGINE_PANEL ? kCtrWords : 16, st));
-    if (p->engine == CDM_ENGINE_WG) {
+    if (!p->gs) HIP_TRY(launch_zero_u32(p->ctr, p->engine == CDM_ENGINE_PANEL ? kCtrWords : 16, st));
+    if (p->gs) {
+        int32_t s2 = solve_gs(p, H, ldh, rhs, lambda, x0, x, inf, st);
+        if (s2) return s2;
+    } else if (p->engine == CDM_ENGINE_WG) {
         ev_record(p, 1, st);
         ev_record(p, 2, st);
         WgLaunch L;
