@@ -1,6 +1,7 @@
 // k_aux.hip -- initial residual, FP64 normal-equation residual, small helpers.
 #include "common.hpp"
 #include "launch.hpp"
+#include "wg.hpp"
 
 namespace cdm {
 
@@ -191,17 +192,7 @@ __global__ void k_fuse(const cv<T>* __restrict__ xloc, const double* __restrict_
                        const double* __restrict__ lam_c, int C, int U, cv<T>* __restrict__ x) {
     const int u = blockIdx.x * blockDim.x + threadIdx.x;
     if (u >= U) return;
-    double tot = 0.0;
-    if (!lam_c)
-        for (int c = 0; c < C; ++c) tot += msum[c] > 0.0 ? 1.0 / msum[c] : 0.0;
-    double re = 0.0, im = 0.0;
-    for (int c = 0; c < C; ++c) {
-        const double wc = lam_c ? lam_c[c] : (msum[c] > 0.0 && tot > 0.0 ? (1.0 / msum[c]) / tot : 0.0);
-        const cv<T> v = xloc[(int64_t)c * U + u];
-        re += wc * (double)v.x;
-        im += wc * (double)v.y;
-    }
-    x[u] = cmake<T>((T)re, (T)im);
+    x[u] = fuse_user<T>(xloc, msum, lam_c, C, U, u);
 }
 hipError_t launch_fuse(bool c128, const void* xloc, const double* msum, const double* lam_c, int C, int U, void* x,
                        hipStream_t st) {

@@ -30,7 +30,7 @@ struct WgLaunch {
     const WgJob* jobs;
     int njobs;
     const int* order; // queue slot -> job id (device), NULL = identity
-    uint32_t* queue;  // device counter, zero before the launch
+    uint32_t* queue;  // device counter, zero before the launch; NULL: workgroup = job (grid = njobs)
     const void* H;
     const void* Y;
     const void* X0;
@@ -44,11 +44,16 @@ struct WgLaunch {
     double rho_c;     // downlink: per-cluster power rho/sqrt(C) (<= 0: no scaling)
     int resid;        // uplink: also write the FP64 normal-equation residual per job
     int rmax = 8;     // largest rows-per-thread tile among the jobs (<= 4 or 8)
+    // without a queue: fuse the jobs' estimates X into fuse_x in the same launch (weights from msum
+    // or fuse_lam; all jobs have n_max users); fuse_count: device word, 0 before and after
+    uint32_t* fuse_count = nullptr;
+    const double* fuse_lam = nullptr;
+    void* fuse_x = nullptr;
 };
 hipError_t launch_wg(const WgLaunch& L, hipStream_t st);
 // Algorithm 2 (downlink ZF precoding), same job and tile conventions; Y is s (U).
 hipError_t launch_zf(const WgLaunch& L, hipStream_t st);
-size_t wg_lds_bytes(int n_max, bool c128);
+size_t wg_lds_bytes(int n_max, bool c128, int nt, int rmax);
 // Mixed-precision refinement of an uneven batch (complex128 H, y, x): per outer step
 // an FP64 residual pass, an FP64 gradient pass (first step: also the low-precision
 // copy Hq and the inner scalars) and the persistent inner-sweep launch.
@@ -86,8 +91,8 @@ size_t bm_lds_bytes(int n_max);
 hipError_t bm_set_lds_limit(int low, int nt, size_t bytes);
 int bm_occupancy(int low, int nt, size_t bytes);
 // rmax: the largest rows-per-thread tile of the launch (<= 4 or 8)
-hipError_t wg_set_lds_limit(bool c128, int nt, int rmax, size_t bytes);
-int wg_occupancy(bool c128, int nt, int rmax, size_t bytes);
+hipError_t wg_set_lds_limit(bool c128, int nt, int rmax, int n_max, size_t bytes);
+int wg_occupancy(bool c128, int nt, int rmax, int n_max, size_t bytes);
 
 // Fusion of C local estimates (Sec. III): x = sum_c lambda_c x_c with
 // lambda_c = sigma_c^-2 / sum_c' sigma_c'^-2 and sigma_c^2 = (N0/U) sum_u m_{u,c}.

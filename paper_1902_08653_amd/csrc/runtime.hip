@@ -212,7 +212,8 @@ static int rpt_for(int m, int nt, int cap = 8) {
 
 // threads per workgroup for single-instance (cluster) plans; the FP64 kernel is kept
 // at <= 512 threads (its 8-rows-per-thread tile does not fit 1024-thread register budgets)
-static int wg_nt_single(int m, bool c128) { return m <= 2048 ? 256 : (c128 ? 512 : 1024); }
+// (at most four rows per thread up to 2048 rows: the panel form of the sweep)
+static int wg_nt_single(int m, bool c128) { return m <= 512 ? 256 : (m <= 2048 || c128 ? 512 : 1024); }
 
 static int32_t setup_wg(cdm_plan* p, int m_max, int n_max, int njobs, int nt) {
     const int cap = 8;
@@ -220,15 +221,15 @@ static int32_t setup_wg(cdm_plan* p, int m_max, int n_max, int njobs, int nt) {
     p->wg_nt = nt;
     p->wg_rpt = rpt_for(m_max, nt, cap);
     p->n_max = std::max(1, n_max);
-    p->wg_lds = p->wg_low ? bm_lds_bytes(p->n_max) : wg_lds_bytes(p->n_max, p->c128);
+    p->wg_lds = p->wg_low ? bm_lds_bytes(p->n_max) : wg_lds_bytes(p->n_max, p->c128, nt, p->wg_rpt);
     if (p->wg_lds + 2048 > kLdsMax) return CDM_ESHAPE;
     if (p->wg_lds > 64 * 1024) {
         const hipError_t e = p->wg_low ? bm_set_lds_limit(p->wg_low, nt, p->wg_lds)
-                                       : wg_set_lds_limit(p->c128, nt, p->wg_rpt, p->wg_lds);
+                                       : wg_set_lds_limit(p->c128, nt, p->wg_rpt, p->n_max, p->wg_lds);
         if (e != hipSuccess) return CDM_ESHAPE;
     }
     const int occ = std::max(1, p->wg_low ? bm_occupancy(p->wg_low, nt, p->wg_lds)
-                                          : wg_occupancy(p->c128, nt, p->wg_rpt, p->wg_lds));
+                                          : wg_occupancy(p->c128, nt, p->wg_rpt, p->n_max, p->wg_lds));
     p->wg_grid = std::max(1, std::min(njobs, occ * p->ncu));
     p->njobs = njobs;
     return CDM_OK;
@@ -822,7 +823,9 @@ int32_t cdm_create(const cdm_desc* desc, cdm_plan** plan) {
             j.rpt = rpt_for(bc[c], p->wg_nt);
             row0 += bc[c];
         }
-        if (hipMemcpy(p->jobs, jobs.data(), sizeof(WgJob) * d.C, hipMemcpyHostToDevice) != hipSuccess) {
+        const uint32_t zeros[16] = {};   // the queue and the fusion count
+        if (hipMemcpy(p->jobs, jobs.data(), sizeof(WgJob) * d.C, hipMemcpyHostToDevice) != hipSuccess ||
+            hipMemcpy(p->ctr, zeros, sizeof(zeros), hipMemcpyHostToDevice) != hipSuccess) {
             (void)hipFree(p->ws);
             delete p;
             return CDM_EHIP;
@@ -921,7 +924,8 @@ int32_t cdm_solve(cdm_plan* p, const void* H, int64_t ldh, const int32_t* rowptr
     if (d.problem == CDM_DOWNLINK_ZF) {
         if (x0) return CDM_EINVAL;
         ev_record(p, 0, st);
-        HIP_TRY(launch_zero_u32(p->ctr, 16, st));
+        const bool each = p->wg_grid == d.C;   // a workgroup per cluster: no queue to clear
+        if (!each) HIP_TRY(launch_zero_u32(p->ctr + 4, 1, st));
         ev_record(p, 1, st);
         ev_record(p, 2, st);
         WgLaunch L;
@@ -933,7 +937,7 @@ int32_t cdm_solve(cdm_plan* p, const void* H, int64_t ldh, const int32_t* rowptr
         L.jobs = p->jobs;
         L.njobs = d.C;
         L.order = nullptr;
-        L.queue = p->ctr + 4;
+        L.queue = each ? nullptr : p->ctr + 4;
         L.H = H;
         L.Y = rhs;
         L.X0 = nullptr;
@@ -965,7 +969,9 @@ int32_t cdm_solve(cdm_plan* p, const void* H, int64_t ldh, const int32_t* rowptr
 
     if (p->mixed) return solve_mixed(p, H, ldh, rhs, lambda, x0, x, inf, st);
     ev_record(p, 0, st);
-    if (!p->gs) HIP_TRY(launch_zero_u32(p->ctr, p->engine == CDM_ENGINE_PANEL ? kCtrWords : 16, st));
+    const bool each = p->engine == CDM_ENGINE_WG && p->wg_grid == d.C;   // a workgroup per cluster: no queue to clear
+    if (p->engine == CDM_ENGINE_PANEL && !p->gs) HIP_TRY(launch_zero_u32(p->ctr, kCtrWords, st));
+    if (p->engine == CDM_ENGINE_WG && !each && !p->gs) HIP_TRY(launch_zero_u32(p->ctr + 4, 1, st));
     if (p->gs) {
         int32_t s2 = solve_gs(p, H, ldh, rhs, lambda, x0, x, inf, st);
         if (s2) return s2;
@@ -981,7 +987,12 @@ int32_t cdm_solve(cdm_plan* p, const void* H, int64_t ldh, const int32_t* rowptr
         L.jobs = p->jobs;
         L.njobs = d.C;
         L.order = nullptr;
-        L.queue = p->ctr + 4;
+        L.queue = each ? nullptr : p->ctr + 4;
+        if (each && d.C > 1) {
+            L.fuse_count = p->ctr + 8;
+            L.fuse_lam = lambda_c;
+            L.fuse_x = x;
+        }
         L.H = H;
         L.Y = rhs;
         L.X0 = x0;
@@ -996,7 +1007,7 @@ int32_t cdm_solve(cdm_plan* p, const void* H, int64_t ldh, const int32_t* rowptr
         L.resid = 0;
         HIP_TRY(launch_wg(L, st));
         ev_record(p, 3, st);
-        if (d.C > 1) HIP_TRY(launch_fuse(p->c128, p->xloc, p->msum, lambda_c, d.C, d.U, x, st));
+        if (d.C > 1 && !each) HIP_TRY(launch_fuse(p->c128, p->xloc, p->msum, lambda_c, d.C, d.U, x, st));
     } else {
         GramLaunch G;
         G.c128 = p->c128;
@@ -1128,12 +1139,12 @@ static double time_batched(cdm_plan* p, int nt, int m_max, int n_max, WgJob* job
     for (auto& j : jj) j.rpt = rpt_for(j.m, nt);
     if (hipMemcpy(jobs_d, jj.data(), sizeof(WgJob) * njobs, hipMemcpyHostToDevice) != hipSuccess) return -1.0;
     const bool mx = p->wg_low != WG_LOW_NONE;
-    const size_t lds = mx ? bm_lds_bytes(std::max(1, n_max)) : wg_lds_bytes(std::max(1, n_max), p->c128);
     const int rmax = rpt_for(m_max, nt);
+    const size_t lds = mx ? bm_lds_bytes(std::max(1, n_max)) : wg_lds_bytes(std::max(1, n_max), p->c128, nt, rmax);
     if (lds > 64 * 1024 &&
-        (mx ? bm_set_lds_limit(p->wg_low, nt, lds) : wg_set_lds_limit(p->c128, nt, rmax, lds)) != hipSuccess)
+        (mx ? bm_set_lds_limit(p->wg_low, nt, lds) : wg_set_lds_limit(p->c128, nt, rmax, std::max(1, n_max), lds)) != hipSuccess)
         return -1.0;
-    const int occ = std::max(1, mx ? bm_occupancy(p->wg_low, nt, lds) : wg_occupancy(p->c128, nt, rmax, lds));
+    const int occ = std::max(1, mx ? bm_occupancy(p->wg_low, nt, lds) : wg_occupancy(p->c128, nt, rmax, std::max(1, n_max), lds));
     WgLaunch L;
     L.c128 = p->c128;
     L.nt = nt;
@@ -1389,6 +1400,11 @@ int32_t cdm_create_batched(const cdm_desc* desc, int32_t batch, const int32_t* m
         if (Ms) (void)hipFree(Ms);
         (void)hipGetLastError();
     }
+    // Plain sweeps with more than 1024 rows: 512 threads, so at most four rows each (the panel
+    // form), while the largest instance's columns one by one (1.3 us each) would take longer than
+    // the batch's stream at 5.7 TB/s; measured even at 0.6 of that time (1500 complex64 instances
+    // of 64..2048 rows: 48.1 against 48.7 ms; 512: 17.9 against 40.5; 4096: 132 against 126).
+    if (nt == 0 && !low && m_max > 1024 && m_max <= 2048 && (double)total_mn * p->esz < 4.4e6 * n_max) nt = 512;
     if (nt == 0) nt = rpt_for(m_max, 256) ? 256 : (rpt_for(m_max, 512) ? 512 : 1024);
     st = setup_wg(p, m_max, n_max, batch, nt);
     if (st) {
@@ -1663,7 +1679,7 @@ extern "C" int32_t cdm_solve_noalloc(const cdm_desc* desc, const void* H, int64_
     const int rmax = rpt_for(bc_max, nt);
     if (rmax == 0) return CDM_ESHAPE;
     for (int c = 0; c < d.C; ++c) ja.rpt[c] = rpt_for(ja.m[c], nt);
-    const size_t lds = wg_lds_bytes(d.U, c128);
+    const size_t lds = wg_lds_bytes(d.U, c128, nt, rmax);
     if (lds + 2048 > kLdsMax) return CDM_ESHAPE;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return CDM_ENODEV;
@@ -1671,8 +1687,8 @@ extern "C" int32_t cdm_solve_noalloc(const cdm_desc* desc, const void* H, int64_
     int ncu = 0;
     int32_t st1 = na_device(dev, &sp, &ncu);
     if (st1) return st1;
-    if (lds > 64 * 1024 && wg_set_lds_limit(c128, nt, rmax, lds) != hipSuccess) return CDM_ESHAPE;
-    const int occ = std::max(1, wg_occupancy(c128, nt, rmax, lds));
+    if (lds > 64 * 1024 && wg_set_lds_limit(c128, nt, rmax, d.U, lds) != hipSuccess) return CDM_ESHAPE;
+    const int occ = std::max(1, wg_occupancy(c128, nt, rmax, d.U, lds));
 
     hipStream_t st = (hipStream_t)stream;
     uint32_t* ctr = (uint32_t*)(sp + kNaCtr);

@@ -5,6 +5,51 @@
 
 namespace cdm {
 
+// Fusion of the local estimates of one instance (Sec. III) for user u:
+// x_hat = sum_c lambda_c x_c with lambda_c = s_c^-1 / sum_c' s_c'^-1, s_c = sum_u m_{u,c}
+// (a cluster without an active coordinate gets 0), or the caller's weights as given.
+template <typename T>
+__device__ __forceinline__ cv<T> fuse_user(const cv<T>* xloc, const double* msum, const double* lam_c, int C, int U,
+                                           int u) {
+    double tot = 0.0;
+    if (!lam_c)
+        for (int c = 0; c < C; ++c) tot += msum[c] > 0.0 ? 1.0 / msum[c] : 0.0;
+    double re = 0.0, im = 0.0;
+    for (int c = 0; c < C; ++c) {
+        const double wc = lam_c ? lam_c[c] : (msum[c] > 0.0 && tot > 0.0 ? (1.0 / msum[c]) / tot : 0.0);
+        const cv<T> v = xloc[(int64_t)c * U + u];
+        re += wc * (double)v.x;
+        im += wc * (double)v.y;
+    }
+    return cmake<T>((T)re, (T)im);
+}
+
+// Fusion in the last workgroup of the clusters' launch (workgroup = cluster): every
+// workgroup releases its estimate and counts itself; the one that counts the last also sets
+// the count back, so that the next launch finds 0.  A launch of its own for this costs more
+// than the solve of a small instance.
+template <typename T> struct WgFuse {
+    uint32_t* count;         // NULL: no fusion here
+    const cv<T>* xloc;
+    const double* msum;
+    const double* lam_c;
+    cv<T>* x;
+    int C, U;
+};
+template <typename T> __device__ __forceinline__ void wg_fuse(const WgFuse<T>& f, int* last_s) {
+    fence_release_agent();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t k = __hip_atomic_fetch_add(f.count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        *last_s = k + 1 == (uint32_t)f.C;
+    }
+    __syncthreads();
+    if (!*last_s) return;
+    fence_acquire_agent();
+    for (int u = threadIdx.x; u < f.U; u += blockDim.x) f.x[u] = fuse_user<T>(f.xloc, f.msum, f.lam_c, f.C, f.U, u);
+    if (threadIdx.x == 0) __hip_atomic_store(f.count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // FP64 stationarity of eq. (1) for one instance held by one workgroup:
 //   ||H^H (y - H x) - lambda x|| / ||H^H y||,
 // with r = y - H x formed in FP64 on the thread's rows (thread t owns rows t, t+NT, ...)
