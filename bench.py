@@ -442,7 +442,7 @@ def bench_sparse(a):
     (Bernoulli pattern, nonzeros CN(0, 1/(0.01 B)), int32 CSR, seed 1), lambda 0.1,
     complex128 (or complex64), plain sweeps to a relative step of 1e-11 (1e-6 for
     complex64), cap 200.  One step = one solve through the C ABI from the CSR arrays:
-    transpose to columns, sparse panel Gram and inverses, init, all sweeps, finalise."""
+    transpose to columns, Gram matrix (or its panels) and inverses, init, all sweeps, finalise."""
     import torch
 
     from paper_1902_08653_amd import cdm, inputs
@@ -489,9 +489,14 @@ def bench_sparse(a):
     xg = x.cpu().numpy().astype(np.complex128)
     sweep_ms = stage["sweeps"] / a.steps
     mean_sweeps = float(np.mean(sweeps))
-    # per sweep: the column values and row indices are read once to gather r and once to
-    # scatter the panel's update back into r
-    alg_bytes = mean_sweeps * 2.0 * nnz * (esz + 4)
+    desc = json.loads(plan.describe())
+    operator = desc.get("schedule") == "operator"
+    kernel = "k_cd_sparse"
+    if operator:    # per sweep: the U^2 complex FP64 values of W
+        kernel = "k_gs_one" if desc["npanels"] == 1 else "k_gs_sweep"
+        alg_bytes = mean_sweeps * 16.0 * a.U * a.U
+    else:           # per sweep: the column values and row indices, once to gather r and once
+        alg_bytes = mean_sweeps * 2.0 * nnz * (esz + 4)    # to scatter the panel's update into r
     achieved = alg_bytes / (sweep_ms * 1e-3) / 1e9
     probes = _hbm_probes(cdm, dev, stream)
     print("[bench] %.3f ms per solve (sweep kernel %.3f ms), sweeps %s" % (ms_per, sweep_ms, sweeps),
@@ -532,14 +537,15 @@ def bench_sparse(a):
                                % (a.B, a.U, density, prec, density, a.seed, a.lam, tol),
                    "B": a.B, "U": a.U, "nnz": nnz, "precision": prec, "tol": tol, "eps": eps,
                    "engine": json.loads(plan.describe())},
-        # frac against HBM is reported as measured; the sweep is a
-        # chain of panel steps (partial, exchange across the slice workgroups, panel product,
-        # scatter) over a MALL-resident operator, so its limiter is that chain's latency
+        # frac against HBM is reported as measured.  The operator's sweep streams W (1 GiB at 8192
+        # users, about a fifth of it from the MALL); the row slices' sweep is a chain of panel
+        # steps over a MALL-resident operator, bound by that chain's latency
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
-                     "traffic": measured_traffic("k_cd_sparse", "%s %dx%d %g tol %g" % (prec, a.B, a.U, density, tol)),
-                     "kernel": "k_cd_sparse",
-                     "limiter": "per-panel exchange latency across the slice workgroups, not HBM",
+                     "traffic": measured_traffic(kernel, "%s %dx%d %g tol %g" % (prec, a.B, a.U, density, tol)),
+                     "kernel": kernel,
+                     "limiter": "W from HBM and the MALL" if operator
+                     else "per-panel exchange latency across the slice workgroups, not HBM",
                      "algorithmic_bytes_per_launch": alg_bytes, "avg_launch_ms": sweep_ms,
                      **_ceiling(achieved, probes)},
         "cpu_baseline": cpu,

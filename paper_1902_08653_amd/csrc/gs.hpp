@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "cdm.h"
+#include "launch.hpp"
 
 namespace cdm {
 
@@ -56,9 +57,16 @@ struct GsLaunch {
     void* r;              // B
     void* b;              // Up
     void* xw;             // Up
+    const SparseLaunch* sp = nullptr;   // CSR input: its column-compressed copy (H is not used)
+    int32_t* kexp = nullptr;            // U: column scales
+    void* vs = nullptr;                 // nnz: scaled values, complex128
     hipEvent_t ev_pre, ev_init, ev_sweep;   // optional stage marks
 };
 hipError_t gs_setup(const GsShape& s);   // LDS limits of the kernels, at plan creation
 hipError_t launch_gs(const GsLaunch& L, hipStream_t st);
+// CSR input (k_gs_sparse.hip): G into L.A, and b (with rows: from x, else from r = y)
+hipError_t gs_sparse_setup(int U);
+hipError_t gs_sparse_matrix(const GsLaunch& L, hipStream_t st);
+hipError_t gs_sparse_refresh(const GsLaunch& L, bool rows, hipStream_t st);
 
 }  // namespace cdm

@@ -666,20 +666,24 @@ __device__ __forceinline__ bool gs_get(const uint64_t* p, int n, int i, uint32_t
     return ((w0 >> 48) == t) & ((w1 >> 48) == t) & ((w2 >> 48) == t);
 }
 
+using gs_v2d = double __attribute__((ext_vector_type(2)));
+
 template <int R, int NW, int KC>
 __global__ __launch_bounds__(64 * (NW + GS_CW), 1) void k_gs_sweep(GsSweepArgs a, int t0, int t1) {
     constexpr int RW = R / NW, k = 64 * KC, GC = KC / GS_CW;
     if (*a.done) return;
     __shared__ double2 bs[2][k];
     __shared__ double2 sacc[2][NW];
+    __shared__ double2 xs[R], xps[R];       // x of these rows and of the sweep before, wave by wave
     __shared__ int go[2][GS_CW];
     extern __shared__ __attribute__((aligned(16))) double2 ms[];   // this workgroup's rows of M: R x k
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int w = blockIdx.x, P = gridDim.x, npan = a.npan, Up = a.Up;
     const int Kw = w * R / k;               // the panel that holds this workgroup's rows
     const bool comm = wid >= NW, lead = wid == NW;
     const int row0 = w * R + (comm ? 0 : wid * RW);
-    double2 b[RW], x[RW], xp[RW], tile[RW][KC];
+    double2 b[RW];
+    double2 tile[RW][KC];
     uint64_t* const xch = a.xch;            // [npan][2] slots of k values
     uint64_t* const sch = a.xch + (int64_t)npan * 2 * k * 3;   // [4] slots of P values
     auto publish = [&](int t) __attribute__((always_inline)) {   // this wave's rows of b for sweep t
@@ -687,11 +691,27 @@ __global__ __launch_bounds__(64 * (NW + GS_CW), 1) void k_gs_sweep(GsSweepArgs a
         for (int r = 0; r < RW; ++r)
             if (lane == r) gs_put(xch + (int64_t)(Kw * 2 + (t & 1)) * k * 3, k, (row0 + r) % k, b[r], (uint32_t)t);
     };
+    // W past 192 MB goes by the MALL (256 MB, which a cyclic stream would empty each time), so
+    // that the first panels stay in it.  8192 users, 1 GiB: 6 of 32 panels cached 206 us a
+    // sweep, all of them 223.
+    const int Kc = (int)(((int64_t)192 << 20) / ((int64_t)16 * Up * k));
     auto load = [&](int K) __attribute__((always_inline)) {
 #pragma unroll
-        for (int r = 0; r < RW; ++r)
+        for (int r = 0; r < RW; ++r) {
+            const double2* const p = a.W + (int64_t)(row0 + r) * Up + K * k;   // scalar base, one offset register
+            uint32_t o = (uint32_t)lane;
+            asm("" : "+v"(o));
+            if (K < Kc) {
 #pragma unroll
-            for (int q = 0; q < KC; ++q) tile[r][q] = a.W[(int64_t)(row0 + r) * Up + K * k + lane + 64 * q];
+                for (int q = 0; q < KC; ++q) tile[r][q] = p[o + 64 * q];
+            } else {
+#pragma unroll
+                for (int q = 0; q < KC; ++q) {
+                    const gs_v2d z = __builtin_nontemporal_load((const gs_v2d*)(p + o + 64 * q));
+                    tile[r][q] = make_double2(z.x, z.y);
+                }
+            }
+        }
     };
     if (!comm) {
 #pragma unroll
@@ -700,7 +720,7 @@ __global__ __launch_bounds__(64 * (NW + GS_CW), 1) void k_gs_sweep(GsSweepArgs a
         load(0);
 #pragma unroll
         for (int r = 0; r < RW; ++r) {
-            x[r] = xp[r] = a.x[row0 + r];
+            if (lane == 0) xs[wid * RW + r] = xps[wid * RW + r] = a.x[row0 + r];
 #pragma unroll
             for (int q = 0; q < KC; ++q)
                 ms[(wid * RW + r) * k + lane + 64 * q] =
@@ -756,10 +776,13 @@ __global__ __launch_bounds__(64 * (NW + GS_CW), 1) void k_gs_sweep(GsSweepArgs a
             const uint64_t* src = xch + (int64_t)(K * 2 + (t & 1)) * k * 3;
             const int i0 = (wid - NW) * 64 * GC + lane;
             double2 v[GC];
+            bool ok = false;
             for (;;) {
-                bool ok = true;
+                if (!ok) {
+                    ok = true;
 #pragma unroll
-                for (int q = 0; q < GC; ++q) ok &= gs_get(src, k, i0 + 64 * q, (uint32_t)t, v[q]);
+                    for (int q = 0; q < GC; ++q) ok &= gs_get(src, k, i0 + 64 * q, (uint32_t)t, v[q]);
+                }
                 if (__all(ok)) break;
                 if (expired()) {
                     g = 3;
@@ -815,11 +838,13 @@ __global__ __launch_bounds__(64 * (NW + GS_CW), 1) void k_gs_sweep(GsSweepArgs a
                     for (int q = 0; q < KC; ++q) cfma(s, ms[(wid * RW + r) * k + lane + 64 * q], v[q]);
                     s.x = group_sum<1>(s.x);
                     s.y = group_sum<1>(s.y);
-                    xp[r] = x[r];
-                    x[r].x += s.x;
-                    x[r].y += s.y;
+                    const double2 xo = xs[wid * RW + r], xn = make_double2(xo.x + s.x, xo.y + s.y);
+                    if (lane == 0) {
+                        xps[wid * RW + r] = xo;
+                        xs[wid * RW + r] = xn;
+                    }
                     s1 += cabs2d(s);
-                    s2 += cabs2d(x[r]);
+                    s2 += cabs2d(xn);
                 }
                 if (lane == 0) sacc[par][wid] = make_double2(s1, s2);
             }
@@ -853,8 +878,7 @@ __global__ __launch_bounds__(64 * (NW + GS_CW), 1) void k_gs_sweep(GsSweepArgs a
     }
     if (!comm && lane == 0) {
 #pragma unroll
-        for (int r = 0; r < RW; ++r)
-            a.x[row0 + r] = make_double2(code == 2 ? xp[r].x : x[r].x, code == 2 ? xp[r].y : x[r].y);
+        for (int r = 0; r < RW; ++r) a.x[row0 + r] = code == 2 ? xps[wid * RW + r] : xs[wid * RW + r];
     }
     if (w == 0 && lead && lane == 0) {
         if (code == 3) gs_info(a.info, t - 1, S, X, a.tol, false);
@@ -877,7 +901,8 @@ __global__ __launch_bounds__(1024) void k_gs_finish(const double2* __restrict__ 
     }
     if (mine) bad = 1;
     __syncthreads();
-    if (threadIdx.x == 0) info->flags |= (int)(*status & CDM_INFO_ZERO_COLUMN) | (bad ? CDM_INFO_NONFINITE : 0);
+    if (threadIdx.x == 0)
+        info->flags |= (int)(*status & (CDM_INFO_ZERO_COLUMN | CDM_INFO_BAD_INPUT)) | (bad ? CDM_INFO_NONFINITE : 0);
 }
 
 // ---- host side -----------------------------------------------------------------------------
@@ -890,11 +915,15 @@ __global__ __launch_bounds__(1024) void k_gs_finish(const double2* __restrict__ 
 
 GsShape gs_shape(int B, int U) {
     GsShape s;
-    s.k = U <= 128 ? 128 : (U <= 256 ? 256 : 512);
+    // panels as wide as the LDS holds R rows of M (128 KB): one exchange per panel and sweep.
+    // R = 16 rows a workgroup up to 4096 users (fewer workgroups poll fewer copies of the same
+    // words: 3000 x 1000, 39 sweeps, 16 rows 818 us, 8 rows 905 us; 256-column panels 1031 us),
+    // 32 above, so that at most 256 workgroups take part
+    s.k = U <= 128 ? 128 : (U <= 256 || U > 4096 ? 256 : 512);
     s.npan = (U + s.k - 1) / s.k;
     s.Up = s.npan * s.k;
     s.one = U <= 128;
-    s.R = s.one ? 128 : 16;
+    s.R = s.one ? 128 : (U > 4096 ? 32 : 16);
     s.P = s.Up / s.R;
     s.nblk = ((U + 63) / 64) * ((U + 63) / 64 + 1) / 2;
     // splits of the rows: fewest rounds of resident workgroups (two per CU) for the work of
@@ -922,6 +951,7 @@ size_t gs_exchange_words(const GsShape& s) {
 static const void* gs_sweep_fn(const GsShape& s) {
     if (s.k == 256 && s.R == 16) return (const void*)k_gs_sweep<16, 8, 4>;
     if (s.k == 512 && s.R == 16) return (const void*)k_gs_sweep<16, 8, 8>;
+    if (s.k == 256 && s.R == 32) return (const void*)k_gs_sweep<32, 8, 4>;
     return nullptr;
 }
 
@@ -940,13 +970,17 @@ template <typename T> static hipError_t launch_gs_t(const GsLaunch& L, hipStream
     hipLaunchKernelGGL(k_gs_init<T>, dim3((nmax + 255) / 256), dim3(256), 0, st, y, (const cv<T>*)L.x0, L.B, L.U, s.Up,
                        r, x, (uint64_t*)L.ctr, (int)(GS_CTR_WORDS / 2 + gs_exchange_words(s)));
     GS_TRY(hipGetLastError());
-    int rps = (L.B + s.nsplit - 1) / s.nsplit;
-    rps = (rps + MK - 1) / MK * MK;
-    hipLaunchKernelGGL(k_gs_gram<T>, dim3(s.nblk, s.nsplit), dim3(256), 0, st, H, L.ld, L.B, L.U, rps,
-                       (double2*)L.gpart, s.nblk);
     const int nb = s.Up / 64;
-    hipLaunchKernelGGL(k_gs_assemble, dim3(nb * (nb + 1) / 2, 4), dim3(256), 0, st, (const double2*)L.gpart, s.nsplit,
-                       s.nblk, s.Up, A);
+    if (L.sp) {
+        GS_TRY(gs_sparse_matrix(L, st));
+    } else {
+        int rps = (L.B + s.nsplit - 1) / s.nsplit;
+        rps = (rps + MK - 1) / MK * MK;
+        hipLaunchKernelGGL(k_gs_gram<T>, dim3(s.nblk, s.nsplit), dim3(256), 0, st, H, L.ld, L.B, L.U, rps,
+                           (double2*)L.gpart, s.nblk);
+        hipLaunchKernelGGL(k_gs_assemble, dim3(nb * (nb + 1) / 2, 4), dim3(256), 0, st, (const double2*)L.gpart,
+                           s.nsplit, s.nblk, s.Up, A);
+    }
     hipLaunchKernelGGL(k_gs_inv64, dim3(nb), dim3(256), GS_INV_LDS, st, A, s.Up, L.U, s.k, L.lambda, M, L.ctr + 3);
     GS_TRY(hipGetLastError());
     for (int h = 64; h < s.k; h *= 2) {
@@ -961,6 +995,7 @@ template <typename T> static hipError_t launch_gs_t(const GsLaunch& L, hipStream
     GS_TRY(hipGetLastError());
     if (L.ev_pre) GS_TRY(hipEventRecord(L.ev_pre, st));
     auto refresh = [&](bool rows) -> hipError_t {
+        if (L.sp) return gs_sparse_refresh(L, rows, st);
         if (rows) {
             hipLaunchKernelGGL(k_gs_rows<T>, dim3((L.B + 15) / 16), dim3(256), 0, st, H, L.ld, L.B, L.U, y, x, r, done);
             GS_TRY(hipGetLastError());

@@ -10,8 +10,8 @@
 // inside the panel is resolved by the inverse M of its small D + L (the block form of the
 // sweep: the same deltas in exact arithmetic), so a panel costs one reduction, one barrier
 // and one pass of dependent steps where eight columns cost eight.  M is formed once per
-// solve (wg_couplings, one read of H) and lives in LDS next to x.  Taller instances, and those whose M does not fit, go column by column
-// (cd_instance).  Measured, column by column / panels: one uneven batch of 512 complex64
+// solve (wg_couplings, one read of H) and lives in LDS next to x.  Taller instances, and
+// those whose M does not fit, go column by column (cd_instance).  Measured, column by column / panels: one uneven batch of 512 complex64
 // instances (m in 64..2048, n = m / 2, to 1e-6) 40.8 / 18.2 ms; four clusters of 250 x 75
 // in complex128, four sweeps, 246 / 67 us.  What bounds it: HBM once the batch fills
 // the chip; a single instance by the chain of its panels (about 0.5 us each) and the FMAs

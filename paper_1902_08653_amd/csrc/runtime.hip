@@ -42,6 +42,7 @@ constexpr double kWgMixedTauC64 = 1e-5;   // inner stop ||delta|| <= tau ||d||: 
 constexpr double kWgMixedTauBf16 = 3e-2;  // BF16 copy (its rounding bounds the outer gain per step)
 constexpr int kCtrWords = 2048;       // control words: counters, abort/status, arrival flags
 constexpr size_t kLdsMax = 160 * 1024;
+constexpr int kGsMaxSparseUsers = 8192;   // a row of G (16 B a user) in LDS
 constexpr int kGsMaxUsers = 2048;     // operator engine: W (U x U complex FP64, 64 MiB) stays in the MALL
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -129,6 +130,8 @@ struct cdm_plan {
     void* gs_r = nullptr;
     void* gs_b = nullptr;
     void* gs_x = nullptr;
+    int32_t* gs_kexp = nullptr;
+    void* gs_vs = nullptr;
     // sparse (CSR input)
     int32_t* sp_colptr = nullptr;
     int32_t* sp_fill = nullptr;
@@ -237,6 +240,8 @@ static int32_t setup_wg(cdm_plan* p, int m_max, int n_max, int njobs, int nt) {
 
 extern "C" int32_t cdm_destroy(cdm_plan* p);
 
+static constexpr int kSpKp = 64;   // users per panel of the sparse row-slice engine
+
 // One instance on the Gauss-Seidel operator (k_gs.hip) instead of the panel engine or one
 // workgroup.  Its pre-pass forms H^H H, 4 B U^2 multiply-adds that the others do not spend
 // (B U^2 / 1.5e7 us); its sweep then costs 4 us per 512 users, against 4-6 us per 64
@@ -321,8 +326,11 @@ static int32_t create_gs(cdm_plan* p, cdm_plan** plan) {
 }
 
 static int32_t solve_gs(cdm_plan* p, const void* H, int64_t ldh, const void* y, double lambda, const void* x0,
-                        void* x, cdm_info* info, hipStream_t st) {
+                        void* x, cdm_info* info, hipStream_t st, const SparseLaunch* sp = nullptr) {
     GsLaunch L;
+    L.sp = sp;
+    L.kexp = p->gs_kexp;
+    L.vs = p->gs_vs;
     L.c128 = p->c128;
     L.s = p->gshape;
     L.B = p->d.B;
@@ -352,13 +360,86 @@ static int32_t solve_gs(cdm_plan* p, const void* H, int64_t ldh, const void* y, 
     return CDM_OK;
 }
 
-static constexpr int kSpKp = 64;
+
+// A sparse instance on the Gauss-Seidel operator: G from nnz^2 / B products, U^2 b / 2 more for W,
+// then U^2 values per sweep from HBM or the MALL, against 5.3 us per panel of 64 users and
+// sweep on the row slices.  Measured, row slices / operator: 16384 x 8192 at 1 % to 1e-11 (57
+// sweeps) 39.4 / 14.6 ms, with 8 sweeps 6.2 / 4.3; 2000 x 1000 at 1 %, 8 sweeps 838 / 328 us; 300
+// x 100 at 5 %, 40 sweeps 613 / 164 us.  Eight sweeps at least (with a tolerance 16 are
+// expected).  Long rows make the products dear (16384 x 2000 at 12 %, 9e8 of them: 114 / 155
+// ms): at most 2e8.  The row of G in LDS bounds the users.
+static bool gs_applies_sparse(const cdm_desc& d) {
+    const int sweeps = d.tol > 0.0 ? std::min(d.T_max, 16) : d.T_max;
+    return d.engine == CDM_ENGINE_AUTO && d.U <= kGsMaxSparseUsers && sweeps >= 8 &&
+           (double)d.nnz * d.nnz <= 2e8 * d.B;
+}
+
+// false: no such plan here (no memory for W and G, 2 GiB at 8192 users), the row slices serve
+static bool create_sparse_gs(cdm_plan* p) {
+    const cdm_desc& d = p->d;
+    const GsShape s = gs_shape(d.B, d.U);
+    if (s.P > p->ncu || gs_setup(s) != hipSuccess || gs_sparse_setup(d.U) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const size_t nnz = (size_t)std::max<int64_t>(d.nnz, 1), sq = 16 * (size_t)s.Up * s.Up;
+    Arena ar;
+    const size_t o_ctr = ar.take(4 * GS_CTR_WORDS + 8 * gs_exchange_words(s));
+    const size_t o_colptr = ar.take(4 * ((size_t)d.U + 1));
+    const size_t o_fill = ar.take(4 * (size_t)d.U);
+    const size_t o_rowidx = ar.take(4 * nnz);
+    const size_t o_cval = ar.take(p->esz * nnz);
+    const size_t o_kexp = ar.take(4 * (size_t)d.U);
+    const size_t o_vs = ar.take(16 * nnz);
+    const size_t o_A = ar.take(sq);
+    const size_t o_W = ar.take(sq);
+    const size_t o_M = ar.take(16 * (size_t)s.npan * s.k * s.k);
+    const size_t o_r = ar.take(16 * (size_t)d.B);
+    const size_t o_b = ar.take(16 * (size_t)s.Up);
+    const size_t o_x = ar.take(16 * (size_t)s.Up);
+    if (alloc_ws(p, ar.off) != CDM_OK) {
+        (void)hipGetLastError();
+        return false;
+    }
+    char* b = p->ws;
+    p->gs = true;
+    p->gshape = s;
+    p->ctr = (uint32_t*)(b + o_ctr);
+    p->sp_colptr = (int32_t*)(b + o_colptr);
+    p->sp_fill = (int32_t*)(b + o_fill);
+    p->sp_rowidx = (int32_t*)(b + o_rowidx);
+    p->sp_cval = b + o_cval;
+    p->gs_kexp = (int32_t*)(b + o_kexp);
+    p->gs_vs = b + o_vs;
+    p->gs_A = b + o_A;
+    p->gs_W = b + o_W;
+    p->M = b + o_M;
+    p->gs_r = b + o_r;
+    p->gs_b = b + o_b;
+    p->gs_x = b + o_x;
+    char buf[512];
+    snprintf(buf, sizeof(buf),
+             "{\"engine\": \"sparse\", \"schedule\": \"operator\", \"precision\": \"%s\", \"B\": %d, \"U\": %d, "
+             "\"nnz\": %lld, \"panel\": %d, \"npanels\": %d, \"workgroups\": %d, \"rows\": %d, \"workspace\": %zu}",
+             p->c128 ? "c128" : "c64", d.B, d.U, (long long)d.nnz, s.k, s.npan, s.one ? 1 : s.P, s.R, p->ws_bytes);
+    p->text = buf;
+    return true;
+}
 
 // Sparse plans: column-compressed copy, panel inverses and residual, all in one
 // workspace sized from desc->nnz.
 static int32_t create_sparse(cdm_plan* p, cdm_plan** plan) {
     const cdm_desc& d = p->d;
     p->engine = 3;
+    if (gs_applies_sparse(d) && create_sparse_gs(p)) {
+        const int32_t st = setup_timing(p);
+        if (st) {
+            cdm_destroy(p);
+            return st;
+        }
+        *plan = p;
+        return CDM_OK;
+    }
     p->kp = kSpKp;
     p->npanels = (d.U + kSpKp - 1) / kSpKp;
     const size_t nnz = (size_t)std::max<int64_t>(d.nnz, 1);
@@ -462,6 +543,10 @@ static int32_t run_sparse(cdm_plan* p, const void* val, const int32_t* rowptr, c
     L.timeout_ticks = p->timeout_ticks;
     L.ev_sweep0 = p->timed ? p->ev[2] : nullptr;
     L.ev_sweep1 = p->timed ? p->ev[3] : nullptr;
+    if (p->gs && !transpose_only) {
+        L.transpose_only = true;   // the operator engine clears its words and asks for the copy
+        return solve_gs(p, nullptr, 0, y, lambda, x0, x, info, st, &L);
+    }
     HIP_TRY(launch_zero_u32(p->ctr, 16, st));
     HIP_TRY(launch_sparse(L, st));
     return CDM_OK;
@@ -962,7 +1047,7 @@ int32_t cdm_solve(cdm_plan* p, const void* H, int64_t ldh, const int32_t* rowptr
         ev_record(p, 1, st);
         int32_t s2 = run_sparse(p, H, rowptr, colidx, rhs, lambda, x0, x, inf, false, st);
         if (s2) return s2;
-        HIP_TRY(launch_finalize(x, d.U, p->c128, p->ctr + 2, inf, st));
+        if (!p->gs) HIP_TRY(launch_finalize(x, d.U, p->c128, p->ctr + 2, inf, st));
         ev_record(p, 4, st);
         return CDM_OK;
     }
