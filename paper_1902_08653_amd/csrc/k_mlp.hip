@@ -638,145 +638,197 @@ hipError_t launch_out_complex(const float* O, void* x, int64_t n, bool c128, hip
     return hipGetLastError();
 }
 
+// ---- the tile product of the fused kernels ----------------------------------------
+// acc[i][q] = sum over k of 64 rows in LDS (i: 16 rows each; BF16, k-fastest, row stride LDA) times
+// 64 columns of W2 (q: 16 columns each) in NK steps of 32.  W2 comes from memory in fragment
+// order ([step][q][lane][8 k], 4 KiB a step), four steps ahead in a ring of registers: a step's
+// loads are issued when its slot has been used, and arrive three steps (about 800 cycles)
+// later.  The ring holds the steps 0..3 on entry and the first four of `wnext` on return.  ROWS:
+// the rows are operand A, so that a lane ends with four rows of one column; else with four
+// columns of one row.
+constexpr int MT_LD = 8;                             // BF16 row padding: conflict-free b128 reads
+typedef bf16x8_t MtRing[4][4];
+__device__ __forceinline__ void mt_fetch(bf16x8_t (&f)[4], const bf16x8_t* step) {
+    uint32_t o = (uint32_t)(threadIdx.x & 63) * 16;  // scalar base, one offset register
+    asm("" : "+v"(o));
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        f[q] = *reinterpret_cast<const bf16x8_t*>(reinterpret_cast<const char*>(step) + o + 1024 * q);
+}
+template <int NK, int LDA, bool ROWS>
+__device__ __forceinline__ void mt_product(f32x4_t (&acc)[4][4], MtRing& f, const bf16x8_t* wf, const bf16x8_t* wnext,
+                                           const unsigned short* rows) {
+    const int lane = threadIdx.x & 63;
+    const unsigned short* const ap = rows + (lane & 15) * LDA + 8 * (lane >> 4);
+    bf16x8_t a[2][4];
+    auto rows_of = [&](int d, int ks) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[d][i] = frag8(ap + 16 * i * LDA + 32 * (ks < NK ? ks : 0));
+    };
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[i][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    rows_of(0, 0);
+#pragma unroll 1
+    for (int k0 = 0; k0 < NK; k0 += 4) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            // the compiler would gather the loads at the loop's end: this order stands
+            rows_of((k + 1) & 1, k0 + k + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    acc[i][q] = ROWS ? mfma32(a[k & 1][i], f[k][q], acc[i][q]) : mfma32(f[k][q], a[k & 1][i], acc[i][q]);
+            __builtin_amdgcn_sched_barrier(0);
+            mt_fetch(f[k], k0 + 4 < NK ? wf + (k0 + k + 4) * 256 : wnext + k * 256);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+// Layer 1 of 16 hidden units and 16 rows by the FP32 matrix instruction (16 x 16 x 4), whose sum is
+// the chain of fused multiply-adds over k ascending from c.  w: lane -> unit lane & 15, x: lane ->
+// row lane & 15, both k = 4 s + (lane >> 4) of step s.
+template <int KS> __device__ __forceinline__ f32x4_t mt_layer1(const float (&a)[KS], const float (&b)[KS], f32x4_t c) {
+#pragma unroll
+    for (int k = 0; k < KS; ++k) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[k], b[k], c, 0, 0, 0);
+    return c;
+}
+template <int KS>
+__device__ __forceinline__ void mt_inputs(float (&xb)[4][KS], const float* X, int64_t r0, int64_t rows, int nin) {
+    const int l16 = threadIdx.x & 15, grp = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const int64_t r = r0 + 16 * i + l16;
+            const int kk = 4 * k + grp;
+            xb[i][k] = bfr((kk < nin && r < rows) ? X[r * nin + kk] : 0.f);   // rows past the end read as 0
+        }
+}
+__device__ __forceinline__ float relu1(float z) { return z > 0.f ? z : 0.f; }
+
 // ---- fused inference (warm-start prediction) -------------------------------------
 // One launch evaluates the whole network for a tile of MI_R rows, with the same
 // operand rounding as the layered forward pass (BF16 operands, FP32 accumulation):
-//   layer 1 (nin <= 16, VALU): A1 = relu(bf16(X) bf16(W1) + b1), kept as BF16 in LDS;
-//   layer 2 (MFMA 16x16x32): Z2 = A1 bf16(W2) + b2 by column blocks of 64 (one 16-column
-//            slice per wave), B fragments straight from a transposed BF16 copy of W2;
+//   layer 1 (nin <= 16, FP32 MFMA): A1 = relu(bf16(X) bf16(W1) + b1), kept as BF16 in LDS;
+//   layer 2 (MFMA 16x16x32): Z2 = A1 bf16(W2) + b2; a wave takes all 64 rows of the columns
+//            64 c + 16 wid + 0..15, four blocks c at a time (4 x 4 tiles: a fragment from LDS or
+//            from W2 serves four MFMAs), W2 in the order in which its fragments are asked for;
 //   layer 3 in the epilogue of each block: Y += bf16(relu(Z2)) bf16(W3), reduced over the
-//            slice's 16 lanes and kept per wave in LDS; the waves' sums are added in a
-//            fixed order at the end and written as the complex warm start.
+//            slice's 16 columns; the waves' sums are added in a fixed order at the end and
+//            written as the complex warm start.
 // Only the activations of one tile ever exist, in LDS: nothing but X and x0 touches HBM.
-constexpr int MI_R = 128;      // rows per workgroup
+// Bound: the matrix cores and the epilogue's VALU work; two workgroups per CU, so that one's
+// runs beside the other's.  262,001 rows, 512 units: 148 us a call (0.93 PFLOP/s); with layer 1 on the
+// VALU, rows along the registers and four shuffles a sum 264 us; 128-row tiles whose waves
+// took 16 columns each, one LDS fragment per MFMA, 424 us.
+constexpr int MI_R = 64;       // rows per workgroup
 constexpr int MI_NT = 256;     // 4 waves
 
-// packed inference weights: W1 and W3 as BF16-rounded FP32, W2 transposed as BF16 bits
+// packed inference weights: W1 and W3 as BF16-rounded FP32; W2 as BF16 bits, fragment by
+// fragment: [slice of 16 columns in 64][column blocks by four][32 k][block][lane][8 k]
 __global__ void k_mlp_pack(const float* __restrict__ w, int nin, int hid, int64_t oW1, int64_t oW2, int64_t oW3,
-                           float* __restrict__ w1r, unsigned short* __restrict__ w2t, float* __restrict__ w3r) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t hh = (int64_t)hid * hid;
-    if (i < hh) {
-        const int n = (int)(i / hid), k = (int)(i % hid);   // w2t[n][k] = W2[k][n]
-        w2t[i] = f32_to_bf16(w[oW2 + (int64_t)k * hid + n]);
+                           float* __restrict__ w1r, unsigned short* __restrict__ w2f, float* __restrict__ w3r) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < hid * hid / 8) {
+        const int lane = i & 63, q = (i >> 6) & 3, nk = hid / 32, ks = (i >> 8) % nk, p = (i >> 8) / nk;
+        const int halves = hid / 256, col = 64 * (4 * (p % halves) + q) + 16 * (p / halves) + (lane & 15);
+        const float* src = w + oW2 + (int64_t)(32 * ks + 8 * (lane >> 4)) * hid + col;
+        uint32_t v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = pack_bf16x2(src[(int64_t)(2 * k) * hid], src[(int64_t)(2 * k + 1) * hid]);
+        reinterpret_cast<uint4*>(w2f)[i] = make_uint4(v[0], v[1], v[2], v[3]);
     }
-    if (i < (int64_t)nin * hid) w1r[i] = __uint_as_float((uint32_t)f32_to_bf16(w[oW1 + i]) << 16);
-    if (i < (int64_t)hid * 2) w3r[i] = __uint_as_float((uint32_t)f32_to_bf16(w[oW3 + i]) << 16);
+    if (i < nin * hid) w1r[i] = bfr(w[oW1 + i]);
+    if (i < hid * 2) w3r[i] = bfr(w[oW3 + i]);
 }
 
-template <int HID, typename V>
-__global__ __launch_bounds__(MI_NT) void k_mlp_infer(const float* __restrict__ X, int64_t rows, int nin,
-                                                     const float* __restrict__ w1r, const float* __restrict__ b1,
-                                                     const unsigned short* __restrict__ w2t,
-                                                     const float* __restrict__ b2, const float* __restrict__ w3r,
-                                                     const float* __restrict__ b3, V* __restrict__ x0) {
-    constexpr int LDA = HID + 8;                     // BF16 row stride of A1 (16 B pad: conflict-free b64 reads)
-    extern __shared__ unsigned char smem_raw[];
+template <int HID, int NIN, typename V>
+__global__ __launch_bounds__(MI_NT, 2) void k_mlp_infer(const float* __restrict__ X, int64_t rows, int nin,
+                                                        const float* __restrict__ w1r, const float* __restrict__ b1,
+                                                        const unsigned short* __restrict__ w2f,
+                                                        const float* __restrict__ b2, const float* __restrict__ w3r,
+                                                        const float* __restrict__ b3, V* __restrict__ x0) {
+    constexpr int LDA = HID + MT_LD, NK = HID / 32, PASS = HID / 256, KS = NIN / 4;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     unsigned short* A1 = reinterpret_cast<unsigned short*>(smem_raw);           // [MI_R][LDA]
-    float* xs = reinterpret_cast<float*>(A1 + MI_R * LDA);                      // [MI_R][16] BF16-rounded X
-    float* yp = xs + MI_R * 16;                                                 // [4 waves][MI_R][2]
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    float* yp = reinterpret_cast<float*>(A1 + MI_R * LDA);                      // [4 waves][MI_R][2]
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, grp = lane >> 4;
     const int64_t r0 = (int64_t)blockIdx.x * MI_R;
-    // ---- stage X (rows past the end read as 0) and clear the layer-3 partials
-    for (int e = tid; e < MI_R * 16; e += MI_NT) {
-        const int r = e >> 4, k = e & 15;
-        const float v = (k < nin && r0 + r < rows) ? X[(r0 + r) * nin + k] : 0.f;
-        xs[e] = __uint_as_float((uint32_t)f32_to_bf16(v) << 16);
-    }
-    for (int e = tid; e < 4 * MI_R * 2; e += MI_NT) yp[e] = 0.f;
-    __syncthreads();
-    // ---- layer 1: thread t owns columns 2t', 2t'+1 (t' = t, t + 256, ... while < HID/2)
-    for (int cp = tid; cp < HID / 2; cp += MI_NT) {
-        const int c = 2 * cp;
-        float wa[16], wb[16];
+    // this wave's fragments of W2: HID / 256 passes of HID / 32 steps of four
+    const bf16x8_t* const wf = reinterpret_cast<const bf16x8_t*>(w2f) + (int64_t)wid * PASS * NK * 256;
+    MtRing f;
+    // ---- layer 1: this wave's HID / 4 hidden units of all 64 rows
+    {
+        float xb[4][KS];
+        mt_inputs<KS>(xb, X, r0, rows, nin);
+#pragma unroll 4
+        for (int m = 0; m < HID / 64; ++m) {
+            const int h0 = wid * (HID / 4) + 16 * m;
+            float wa[KS];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            wa[k] = k < nin ? w1r[(int64_t)k * HID + c] : 0.f;
-            wb[k] = k < nin ? w1r[(int64_t)k * HID + c + 1] : 0.f;
-        }
-        const float ba = b1[c], bb = b1[c + 1];
-        for (int r = 0; r < MI_R; ++r) {
-            float za = 0.f, zb = 0.f;
+            for (int k = 0; k < KS; ++k) wa[k] = 4 * k + grp < nin ? w1r[(4 * k + grp) * HID + h0 + l16] : 0.f;
+            const float4 b = *reinterpret_cast<const float4*>(b1 + h0 + 4 * grp);
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const float xv = xs[r * 16 + k];
-                za += xv * wa[k];
-                zb += xv * wb[k];
+            for (int i = 0; i < 4; ++i) {
+                const f32x4_t z = mt_layer1<KS>(wa, xb[i], f32x4_t{0.f, 0.f, 0.f, 0.f});
+                *reinterpret_cast<uint2*>(&A1[(16 * i + l16) * LDA + h0 + 4 * grp]) =
+                    make_uint2(pack_bf16x2(relu1(z[0] + b.x), relu1(z[1] + b.y)),
+                               pack_bf16x2(relu1(z[2] + b.z), relu1(z[3] + b.w)));
             }
-            za += ba;
-            zb += bb;
-            const uint32_t pa = f32_to_bf16(za > 0.f ? za : 0.f), pb = f32_to_bf16(zb > 0.f ? zb : 0.f);
-            *reinterpret_cast<uint32_t*>(&A1[r * LDA + c]) = pa | (pb << 16);
         }
     }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) mt_fetch(f[k], wf + k * 256);
     __syncthreads();
     // ---- layers 2 and 3
-    const int kq = 8 * (lane >> 4);                  // this lane's k offset inside a 32-step
-    float y0[MI_R / 16][4], y1[MI_R / 16][4];        // layer-3 partials of this lane's rows
+    float y0[4][4], y1[4][4];                        // layer-3 partials of this lane's row 16 i + l16
 #pragma unroll
-    for (int i = 0; i < MI_R / 16; ++i)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) y0[i][r] = y1[i][r] = 0.f;
-    for (int nb = 0; nb < HID; nb += 64) {
-        const int col = nb + 16 * wid + (lane & 15);
-        const unsigned short* bsrc = w2t + (int64_t)col * HID + kq;
-        f32x4_t acc[MI_R / 16];
-#pragma unroll
-        for (int i = 0; i < MI_R / 16; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-        // B fragments in groups of 4 thirty-two-steps of K: the next group's 4 loads are in
-        // flight while the current group's MFMAs run (one L2 round trip per group)
-        constexpr int GRP = 4;
-        bf16x8_t cur[GRP], nxt[GRP];
-#pragma unroll
-        for (int k = 0; k < GRP; ++k) cur[k] = frag8(bsrc + 32 * k);
 #pragma unroll 1
-        for (int k0 = 0; k0 < HID; k0 += 32 * GRP) {
-            if (k0 + 32 * GRP < HID) {
+    for (int p = 0; p < PASS; ++p) {
+        f32x4_t acc[4][4];
+        mt_product<NK, LDA, false>(acc, f, wf + p * NK * 256, wf + (p + 1 < PASS ? p + 1 : 0) * NK * 256, A1);
+        // epilogue: lane holds Z2[16 i + l16][col .. col + 3]
 #pragma unroll
-                for (int k = 0; k < GRP; ++k) nxt[k] = frag8(bsrc + k0 + 32 * GRP + 32 * k);
-            }
+        for (int q = 0; q < 4; ++q) {
+            const int col = 64 * (4 * p + q) + 16 * wid + 4 * grp;
+            const float4 bz = *reinterpret_cast<const float4*>(b2 + col);
+            const float4 wa = *reinterpret_cast<const float4*>(w3r + 2 * col);
+            const float4 wb = *reinterpret_cast<const float4*>(w3r + 2 * col + 4);
+            const float bb[4] = {bz.x, bz.y, bz.z, bz.w}, w0[4] = {wa.x, wa.z, wb.x, wb.z}, w1[4] = {wa.y, wa.w, wb.y, wb.w};
 #pragma unroll
-            for (int k = 0; k < GRP; ++k) {
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int i = 0; i < MI_R / 16; ++i)
-                    acc[i] = mfma32(frag8(&A1[(16 * i + (lane & 15)) * LDA + k0 + 32 * k + kq]), cur[k], acc[i]);
-            }
-#pragma unroll
-            for (int k = 0; k < GRP; ++k) cur[k] = nxt[k];
+                for (int r = 0; r < 4; r += 2) {
+                    const float za = acc[i][q][r] + bb[r], zb = acc[i][q][r + 1] + bb[r + 1];
+                    const uint32_t pk = pack_bf16x2(relu1(za), relu1(zb));
+                    const float a2 = __uint_as_float(pk << 16), a3 = __uint_as_float(pk & 0xffff0000u);
+                    y0[i][r] += a2 * w0[r];
+                    y1[i][r] += a2 * w1[r];
+                    y0[i][r + 1] += a3 * w0[r + 1];
+                    y1[i][r + 1] += a3 * w1[r + 1];
+                }
         }
-        // epilogue: lane holds Z2[16 i + 4 (lane >> 4) + r][col]
-        const float bz = b2[col];
-        const float wo0 = w3r[(int64_t)col * 2], wo1 = w3r[(int64_t)col * 2 + 1];
-#pragma unroll
-        for (int i = 0; i < MI_R / 16; ++i)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const float z = acc[i][r] + bz;
-                const float a2 = __uint_as_float((uint32_t)f32_to_bf16(z > 0.f ? z : 0.f) << 16);
-                y0[i][r] += a2 * wo0;
-                y1[i][r] += a2 * wo1;
-            }
     }
-    // sum over the 16 lanes of each row group (the wave's columns), then per wave into LDS
+    // sum over the slice's 16 columns (four in this lane, four lanes), then per wave into LDS
 #pragma unroll
-    for (int i = 0; i < MI_R / 16; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            float a = y0[i][r], b = y1[i][r];
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) {
-                a += __shfl_xor(a, o);
-                b += __shfl_xor(b, o);
-            }
-            if ((lane & 15) == 0) {
-                const int row = 16 * i + 4 * (lane >> 4) + r;
-                yp[(wid * MI_R + row) * 2 + 0] = a;
-                yp[(wid * MI_R + row) * 2 + 1] = b;
-            }
-        }
+    for (int i = 0; i < 4; ++i) {
+        float s0 = (y0[i][0] + y0[i][1]) + (y0[i][2] + y0[i][3]), s1 = (y1[i][0] + y1[i][1]) + (y1[i][2] + y1[i][3]);
+        s0 += __shfl_xor(s0, 16);
+        s1 += __shfl_xor(s1, 16);
+        s0 += __shfl_xor(s0, 32);
+        s1 += __shfl_xor(s1, 32);
+        if (grp == 0) *reinterpret_cast<float2*>(&yp[(wid * MI_R + 16 * i + l16) * 2]) = make_float2(s0, s1);
+    }
     __syncthreads();
     if (tid < MI_R && r0 + tid < rows) {
-        float o0 = b3[0], o1 = b3[1];
         float s0 = 0.f, s1 = 0.f;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
@@ -784,40 +836,29 @@ __global__ __launch_bounds__(MI_NT) void k_mlp_infer(const float* __restrict__ X
             s1 += yp[(w * MI_R + tid) * 2 + 1];
         }
         V v;
-        v.x = s0 + o0;
-        v.y = s1 + o1;
+        v.x = s0 + b3[0];
+        v.y = s1 + b3[1];
         x0[r0 + tid] = v;
     }
 }
 
-size_t mlp_infer_lds(int hid) { return (size_t)MI_R * (hid + 8) * 2 + (size_t)MI_R * 16 * 4 + 4 * MI_R * 2 * 4; }
-
 // hid in {256, 512}; nin <= 16; nout = 2
 hipError_t launch_mlp_infer(const float* w, int nin, int hid, int64_t oW1, int64_t ob1, int64_t oW2, int64_t ob2,
-                            int64_t oW3, int64_t ob3, float* w1r, unsigned short* w2t, float* w3r, const float* X,
+                            int64_t oW3, int64_t ob3, float* w1r, unsigned short* w2f, float* w3r, const float* X,
                             int64_t rows, void* x0, bool c128, hipStream_t st) {
-    const int64_t pk = std::max<int64_t>((int64_t)hid * hid, (int64_t)nin * hid);
+    const int pk = hid * hid / 8;                    // >= nin hid, 2 hid
     hipLaunchKernelGGL(k_mlp_pack, dim3((unsigned)((pk + 255) / 256)), dim3(256), 0, st, w, nin, hid, oW1, oW2, oW3,
-                       w1r, w2t, w3r);
-    const size_t lds = mlp_infer_lds(hid);
+                       w1r, w2f, w3r);
+    const size_t lds = (size_t)MI_R * (hid + MT_LD) * 2 + 4 * MI_R * 2 * 4;
     const dim3 grid((unsigned)((rows + MI_R - 1) / MI_R));
-#define CDM_MI_LAUNCH(H_, V_)                                                                                     \
-    do {                                                                                                         \
-        hipError_t e_ = hipFuncSetAttribute((const void*)k_mlp_infer<H_, V_>,                                    \
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);               \
-        if (e_ != hipSuccess) return e_;                                                                         \
-        hipLaunchKernelGGL((k_mlp_infer<H_, V_>), grid, dim3(MI_NT), lds, st, X, rows, nin, w1r, w + ob1, w2t,   \
-                           w + ob2, w3r, w + ob3, (V_*)x0);                                                      \
-    } while (0)
-    if (hid == 512) {
-        if (c128) CDM_MI_LAUNCH(512, double2);
-        else CDM_MI_LAUNCH(512, float2);
-    } else if (hid == 256) {
-        if (c128) CDM_MI_LAUNCH(256, double2);
-        else CDM_MI_LAUNCH(256, float2);
-    } else {
-        return hipErrorInvalidValue;
-    }
+#define CDM_MI_LAUNCH(H_, N_, V_)                                                                                    do {                                                                                                                 hipError_t e_ = hipFuncSetAttribute((const void*)k_mlp_infer<H_, N_, V_>,                                                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                       if (e_ != hipSuccess) return e_;                                                                                 hipLaunchKernelGGL((k_mlp_infer<H_, N_, V_>), grid, dim3(MI_NT), lds, st, X, rows, nin, w1r, w + ob1,                               w2f, w + ob2, w3r, w + ob3, (V_*)x0);                                                     } while (0)
+#define CDM_MI_TYPE(H_, N_)                                                                                          do {                                                                                                                 if (c128) CDM_MI_LAUNCH(H_, N_, double2);                                                                        else CDM_MI_LAUNCH(H_, N_, float2);                                                                          } while (0)
+    if (hid == 512 && nin <= 8) CDM_MI_TYPE(512, 8);
+    else if (hid == 512) CDM_MI_TYPE(512, 16);
+    else if (hid == 256 && nin <= 8) CDM_MI_TYPE(256, 8);
+    else if (hid == 256) CDM_MI_TYPE(256, 16);
+    else return hipErrorInvalidValue;
+#undef CDM_MI_TYPE
 #undef CDM_MI_LAUNCH
     return hipGetLastError();
 }
@@ -837,7 +878,7 @@ struct Mlp {
     float* splitk = nullptr;                  // split-K partial products of the weight gradients
     int64_t splitk_floats = 0;
     float *w1r = nullptr, *w3r = nullptr;     // fused inference: BF16-rounded W1, W3
-    unsigned short* w2t = nullptr;            // and W2 transposed as BF16
+    unsigned short* w2f = nullptr;            // and W2 as BF16 in fragment order
     bool fused = false;                       // shape served by k_mlp_infer
     void* ws = nullptr;
     int64_t step = 0;
@@ -1011,9 +1052,10 @@ int32_t cdm_mlp_create(int32_t nin, int32_t h1, int32_t h2, int32_t nout, int32_
     n->splitk_floats = skf;
     p += skf;
     if (n->fused) {
+        p += -(p - (float*)n->ws) & 3;   // 16-B aligned
         n->w1r = p; p += (int64_t)nin * h1;
-        n->w3r = p; p += 2 * (int64_t)h2 + 64;
-        n->w2t = reinterpret_cast<unsigned short*>(p);
+        n->w3r = p; p += 2 * (int64_t)h2 + 60;
+        n->w2f = reinterpret_cast<unsigned short*>(p);
     }
     if (hipMemset(n->m1, 0, sizeof(float) * 2 * n->nparam) != hipSuccess) {
         (void)hipFree(n->ws);
@@ -1080,7 +1122,7 @@ int32_t cdm_mlp_predict(cdm_mlp* n, const float* X, int64_t rows, void* x0, int3
     const bool c128 = precision == CDM_C128;
     const size_t esz = c128 ? 16 : 8;
     if (n->fused) {   // one launch, activations in LDS only
-        MLP_TRY(launch_mlp_infer(n->w, n->nin, n->h1, n->oW1, n->ob1, n->oW2, n->ob2, n->oW3, n->ob3, n->w1r, n->w2t,
+        MLP_TRY(launch_mlp_infer(n->w, n->nin, n->h1, n->oW1, n->ob1, n->oW2, n->ob2, n->oW3, n->ob3, n->w1r, n->w2f,
                                  n->w3r, X, rows, x0, c128, st));
         return CDM_OK;
     }
