@@ -863,6 +863,452 @@ hipError_t launch_mlp_infer(const float* w, int nin, int hid, int64_t oW1, int64
     return hipGetLastError();
 }
 
+// ---- fused training pass ------------------------------------------------------------
+// Everything of one step that stays within a row, for a tile of 64 rows and HID / 64 waves: the
+// forward pass, the error and its gradient, dZ2, dZ1 and the tile's sums for W1, b1, b2, W3 and b3.
+// The operands and sums are those of the layered pass (BF16 operands, FP32 accumulation, each
+// layer's chain in the same order); no activation is read back from HBM.  For the one product
+// over rows, W2's gradient (k_mlp_dw), the tile leaves A1 and dZ2 as BF16 fragments over 32 rows:
+// lane -> unit lane & 15, its 8 values the rows 4 g .. 4 g + 3 of both 16-row halves (g = lane >> 4),
+// which is how the matrix instructions leave them; both operands are in this order.
+// Layers:
+//   1   twice on FP32 MFMA: a lane's four units of a row for LDS, four rows of a unit for the
+//       fragments (cheaper than transposing);
+//   2   as in k_mlp_infer; W2's columns are dealt to waves and tiles so that a lane meets the
+//       columns congruent mod 64 one after the other, the order of the layered output layer;
+//   3   the 64 partial sums of a row over LDS, one thread per row and output;
+//   dZ2 two columns per thread: LDS (in place of A2), fragments, sums of dZ2 and A2^T dO;
+//   dZ1 the second product; its four rows per lane are at once an operand of X^T dZ1
+//       (16 x 16 x 16 MFMA).
+// LDS (512 units: 140 KB) allows one workgroup per CU: bound by the latency of its phases (28 % of
+// its cycles in MFMA).  16,384 rows, 512 units: 33 us, in the place of ten launches of 226 us.
+typedef short bf16x4s_t __attribute__((ext_vector_type(4)));
+constexpr int MTR_R = 64, MTR_Y = 68;   // rows per tile; row stride of layer 3's partial sums
+// offsets in a tile's sums: W1 and b1, b2, W3, b3
+__host__ __device__ inline int mtr_sums(int nin, int hid) { return (nin + 1) * hid + hid + 2 * hid + 2; }
+// bytes of LDS for A2, which the partial sums of layer 3 use first
+template <int HID> constexpr int mtr_a2() { return HID == 512 ? 2 * MTR_R * (HID + MT_LD) : 8 * MTR_R * MTR_Y; }
+// first column of pair h (registers 2 h, 2 h + 1) of lane group g, tile q, wave w
+template <int HID> __device__ __forceinline__ int mtr_col(int w, int q, int g, int h) {
+    return HID == 512 ? 64 * (2 * q + h) + 8 * w + 2 * g : 64 * q + 16 * w + 4 * g + 2 * h;
+}
+
+// W1 and W3 rounded; W2 in fragment order of the forward (w2f: A operand, columns of mtr_col) and
+// backward (w2b: B operand, units 64 w + 16 q + (lane & 15)) products: [w][step][q][lane][8]
+template <int HID>
+__global__ __launch_bounds__(256) void k_mlp_pack_train(const float* __restrict__ w, int nin, int64_t oW1, int64_t oW2,
+                                                        int64_t oW3, float* __restrict__ w1r,
+                                                        unsigned short* __restrict__ w2f,
+                                                        unsigned short* __restrict__ w2b, float* __restrict__ w3r) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < HID * HID / 8) {
+        const int lane = i & 63, q = (i >> 6) & 3, ks = (i >> 8) % (HID / 32), wv = (i >> 8) / (HID / 32);
+        const int m = lane & 15, k = 32 * ks + 8 * (lane >> 4);
+        const int col = mtr_col<HID>(wv, q, m >> 2, (m & 3) >> 1) + (m & 1);
+        const float* src = w + oW2 + (int64_t)k * HID + col;
+        uint32_t v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = pack_bf16x2(src[(2 * j) * HID], src[(2 * j + 1) * HID]);
+        reinterpret_cast<uint4*>(w2f)[i] = make_uint4(v[0], v[1], v[2], v[3]);
+        const float* row = w + oW2 + (int64_t)(64 * wv + 16 * q + m) * HID + k;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = pack_bf16x2(row[2 * j], row[2 * j + 1]);
+        reinterpret_cast<uint4*>(w2b)[i] = make_uint4(v[0], v[1], v[2], v[3]);
+    }
+    if (i < nin * HID) w1r[i] = bfr(w[oW1 + i]);
+    if (i < 2 * HID) w3r[i] = bfr(w[oW3 + i]);
+}
+
+template <int HID, int NIN>
+__global__ __launch_bounds__(HID, 1) void k_mlp_train(const float* __restrict__ X, const float* __restrict__ Tg, int rows,
+                                                      int nin, float scale, const float* __restrict__ w1r,
+                                                      const float* __restrict__ b1,
+                                                      const unsigned short* __restrict__ w2f,
+                                                      const unsigned short* __restrict__ w2b,
+                                                      const float* __restrict__ b2, const float* __restrict__ w3r,
+                                                      const float* __restrict__ b3, uint4* __restrict__ a1f,
+                                                      uint4* __restrict__ dzf, float* __restrict__ sums,
+                                                      float* __restrict__ sq) {
+    constexpr int LDA = HID + MT_LD, NK = HID / 32, KS = NIN / 4, NT = HID / 16, NY = HID == 512 ? 2 : 4;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    unsigned short* A1 = reinterpret_cast<unsigned short*>(smem_raw);           // [64][LDA]
+    unsigned short* A2 = A1 + MTR_R * LDA;                                      // [64][LDA]: A2, then dZ2
+    float* ys = reinterpret_cast<float*>(A2);                                   // [2][64][MTR_Y], before A2
+    float* o16 = reinterpret_cast<float*>(smem_raw + 2 * MTR_R * LDA + mtr_a2<HID>());   // [64][2] dO as BF16
+    float* half = o16 + 2 * MTR_R;                                              // [6][HID / 2]
+    const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, grp = lane >> 4;
+    const int64_t r0 = (int64_t)blockIdx.x * MTR_R;
+    float* const my = sums + (int64_t)blockIdx.x * mtr_sums(nin, HID);
+    const bf16x8_t* const wf = reinterpret_cast<const bf16x8_t*>(w2f) + wid * NK * 256;
+    const bf16x8_t* const wb = reinterpret_cast<const bf16x8_t*>(w2b) + wid * NK * 256;
+    MtRing f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) mt_fetch(f[k], wf + k * 256);
+    // ---- layer 1: units 64 wid .. + 63
+    {
+        float xb[4][KS];
+        mt_inputs<KS>(xb, X, r0, rows, nin);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int h0 = 64 * wid + 16 * m;
+            float wa[KS];
+#pragma unroll
+            for (int k = 0; k < KS; ++k) wa[k] = 4 * k + grp < nin ? w1r[(4 * k + grp) * HID + h0 + l16] : 0.f;
+            const float4 b = *reinterpret_cast<const float4*>(b1 + h0 + 4 * grp);
+            const float bl = b1[h0 + l16];
+            uint32_t fr[4][2];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const f32x4_t z = mt_layer1<KS>(wa, xb[i], f32x4_t{b.x, b.y, b.z, b.w});
+                *reinterpret_cast<uint2*>(&A1[(16 * i + l16) * LDA + h0 + 4 * grp]) =
+                    make_uint2(pack_bf16x2(relu1(z[0]), relu1(z[1])), pack_bf16x2(relu1(z[2]), relu1(z[3])));
+                const f32x4_t v = mt_layer1<KS>(xb[i], wa, f32x4_t{bl, bl, bl, bl});
+                fr[i][0] = pack_bf16x2(relu1(v[0]), relu1(v[1]));
+                fr[i][1] = pack_bf16x2(relu1(v[2]), relu1(v[3]));
+            }
+#pragma unroll
+            for (int I = 0; I < 2; ++I)
+                a1f[((int64_t)(2 * blockIdx.x + I) * NT + 4 * wid + m) * 64 + lane] =
+                    make_uint4(fr[2 * I][0], fr[2 * I][1], fr[2 * I + 1][0], fr[2 * I + 1][1]);
+        }
+    }
+    __syncthreads();
+    // ---- layer 2, and the partial sums of layer 3
+    f32x4_t acc[4][4];
+    mt_product<NK, LDA, false>(acc, f, wf, wb, A1);
+    uint32_t a2[4][4][2];
+    {
+        float y[2][4][NY];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int r = 0; r < NY; ++r) y[0][i][r] = y[1][i][r] = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int col = mtr_col<HID>(wid, q, grp, h), c = NY == 2 ? 0 : 2 * h;
+                const float2 bz = *reinterpret_cast<const float2*>(b2 + col);
+                const float4 wo = *reinterpret_cast<const float4*>(w3r + 2 * col);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t pk = pack_bf16x2(relu1(acc[i][q][2 * h] + bz.x), relu1(acc[i][q][2 * h + 1] + bz.y));
+                    const float u = __uint_as_float(pk << 16), v = __uint_as_float(pk & 0xffff0000u);
+                    y[0][i][c] += u * wo.x;
+                    y[1][i][c] += u * wo.y;
+                    y[0][i][c + 1] += v * wo.z;
+                    y[1][i][c + 1] += v * wo.w;
+                    a2[i][q][h] = pk;
+                }
+            }
+        const int res = HID == 512 ? 8 * wid + 2 * grp : 16 * wid + 4 * grp;     // column mod 64
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int r = 0; r < NY; r += 2)
+                    *reinterpret_cast<float2*>(&ys[(j * MTR_R + 16 * i + l16) * MTR_Y + res + r]) =
+                        make_float2(y[j][i][r], y[j][i][r + 1]);
+    }
+    __syncthreads();
+    // ---- layer 3, the error and its gradient: thread -> row lane, output wid
+    if (wid < 2) {
+        float v[64];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const float4 t = *reinterpret_cast<const float4*>(&ys[(wid * MTR_R + lane) * MTR_Y + 4 * k]);
+            v[4 * k] = t.x;
+            v[4 * k + 1] = t.y;
+            v[4 * k + 2] = t.z;
+            v[4 * k + 3] = t.w;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+            for (int k = 0; k < o; ++k) v[k] += v[k + o];
+        const int64_t e = (r0 + lane) * 2 + wid;
+        const bool in = r0 + lane < rows;
+        const float d = in ? (v[0] + b3[wid]) - Tg[e] : 0.f;
+        const float g = 2.f * d * scale;
+        if (in) sq[e] = d * d;
+        o16[2 * lane + wid] = bfr(g);
+        const float t = wave_allsum(g);
+        if (lane == 0) my[(nin + 1) * HID + 3 * HID + wid] = t;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                *reinterpret_cast<uint32_t*>(&A2[(16 * i + l16) * LDA + mtr_col<HID>(wid, q, grp, h)]) = a2[i][q][h];
+    __syncthreads();
+    // ---- dZ2 = (dO W3^T) [A2 > 0]: thread -> columns c, c + 1 of the 32 rows of half I
+    {
+        const int c = 2 * (tid % (HID / 2)), I = tid / (HID / 2);
+        const float4 wo = *reinterpret_cast<const float4*>(w3r + 2 * c);
+        float cs0 = 0.f, cs1 = 0.f, aw[4] = {0.f, 0.f, 0.f, 0.f};
+        uint4* const out = dzf + ((int64_t)(2 * blockIdx.x + I) * NT + c / 16) * 64 + c % 16;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            uint32_t p0[4], p1[4];
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) {
+                float d0[2], d1[2];
+                const int row = 32 * I + (e < 4 ? 4 * g + e : 12 + 4 * g + e);
+                unsigned short* const at = &A2[row * LDA + c];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const uint32_t u = *reinterpret_cast<const uint32_t*>(at + t * LDA);
+                    const float a = __uint_as_float(u << 16), b = __uint_as_float(u & 0xffff0000u);
+                    const float2 o = *reinterpret_cast<const float2*>(&o16[2 * (row + t)]);
+                    const float da = o.x * wo.x + o.y * wo.y, db = o.x * wo.z + o.y * wo.w;
+                    d0[t] = a > 0.f ? da : 0.f;
+                    d1[t] = b > 0.f ? db : 0.f;
+                    cs0 += d0[t];
+                    cs1 += d1[t];
+                    aw[0] += a * o.x;
+                    aw[1] += a * o.y;
+                    aw[2] += b * o.x;
+                    aw[3] += b * o.y;
+                }
+                p0[e / 2] = pack_bf16x2(d0[0], d0[1]);
+                p1[e / 2] = pack_bf16x2(d1[0], d1[1]);
+                *reinterpret_cast<uint32_t*>(at) = (p0[e / 2] & 0xffffu) | (p1[e / 2] << 16);
+                *reinterpret_cast<uint32_t*>(at + LDA) = (p0[e / 2] >> 16) | (p1[e / 2] & 0xffff0000u);
+            }
+            out[16 * g] = make_uint4(p0[0], p0[1], p0[2], p0[3]);
+            out[16 * g + 1] = make_uint4(p1[0], p1[1], p1[2], p1[3]);
+        }
+        float s[6] = {cs0, cs1, aw[0], aw[1], aw[2], aw[3]};
+        if (I == 1) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) half[k * (HID / 2) + c / 2] = s[k];
+        }
+        __syncthreads();
+        if (I == 0) {
+#pragma unroll
+            for (int k = 0; k < 6; ++k) s[k] += half[k * (HID / 2) + c / 2];
+            float* const p = my + (nin + 1) * HID;
+            p[c] = s[0];
+            p[c + 1] = s[1];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[HID + 2 * c + k] = s[2 + k];
+        }
+    }
+    // ---- dZ1 = (dZ2 W2^T) [A1 > 0], X^T dZ1 and the column sums
+    mt_product<NK, LDA, true>(acc, f, wb, wb, A2);
+    bf16x4s_t xt[4];                                 // X^T: input l16, rows 16 i + 4 grp + 0..3
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float x[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t r = r0 + 16 * i + 4 * grp + e;
+            x[e] = (l16 < nin && r < rows) ? X[r * nin + l16] : 0.f;
+        }
+        const uint2 u = make_uint2(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]));
+        xt[i] = __builtin_bit_cast(bf16x4s_t, u);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int hu = 64 * wid + 16 * q + l16;
+        f32x4_t dw = {0.f, 0.f, 0.f, 0.f};
+        float cs = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                v[r] = A1[(16 * i + 4 * grp + r) * LDA + hu] ? acc[i][q][r] : 0.f;
+                cs += v[r];
+            }
+            const uint2 u = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+            dw = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(xt[i], __builtin_bit_cast(bf16x4s_t, u), dw, 0, 0, 0);
+        }
+        cs += __shfl_xor(cs, 16);
+        cs += __shfl_xor(cs, 32);
+        if (grp == 0) my[nin * HID + hu] = cs;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (4 * grp + r < nin) my[(4 * grp + r) * HID + hu] = dw[r];
+    }
+}
+
+// W2's gradient A1^T dZ2 from the fragments: 128 x 128 tile per workgroup (four waves of 64 x 64),
+// blocks [z per, z per + per) of 32 rows into part + z HID^2.  The fragments are read as they lie,
+// without LDS: 8 KiB for 16 MFMAs of a wave, half of them hits of the L1 (its other row or
+// column of waves).  Bound by fetching the fragments from the MALL: 16,384 rows, 512 units 16 us
+// (20 us with a split's tiles spread over the XCDs; 60 us from FP32 activations through LDS).
+template <int HID>
+__global__ __launch_bounds__(256, 1) void k_mlp_dw(const bf16x8_t* __restrict__ a1f, const bf16x8_t* __restrict__ dzf,
+                                                   int nblk, int per, float* __restrict__ part) {
+    constexpr int NT = HID / 16, TW = HID / 128, RING = 4;
+    // workgroups go to the 8 XCDs in turn: the tiles of a split stay on one, whose L2 holds its rows
+    const int tile = (blockIdx.x / 8) % (TW * TW), z = blockIdx.x % 8 + 8 * (blockIdx.x / (8 * TW * TW));
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int m0 = 128 * (tile / TW) + 64 * (wid >> 1), n0 = 128 * (tile % TW) + 64 * (wid & 1);
+    const int k0 = z * per, k1 = min(nblk, k0 + per);
+    if (k0 >= k1) return;
+    bf16x8_t a[RING][4], b[RING][4];
+    auto fetch = [&](int s, int k) __attribute__((always_inline)) {
+        k = k < k1 ? k : k1 - 1;
+        mt_fetch(a[s], a1f + ((int64_t)k * NT + m0 / 16) * 64);
+        mt_fetch(b[s], dzf + ((int64_t)k * NT + n0 / 16) * 64);
+    };
+    f32x4_t acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[i][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    auto mma = [&](int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[i][q] = mfma32(a[s][i], b[s][q], acc[i][q]);
+    };
+#pragma unroll
+    for (int s = 0; s < RING; ++s) fetch(s, k0 + s);
+    int k = k0;
+#pragma unroll 1
+    for (; k + RING <= k1; k += RING) {
+#pragma unroll
+        for (int s = 0; s < RING; ++s) {
+            mma(s);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(s, k + s + RING);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < RING; ++s)
+        if (k + s < k1) mma(s);
+    float* const out = part + (int64_t)z * HID * HID;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                out[(m0 + 16 * i + 4 * (lane >> 4) + r) * HID + n0 + 16 * q + (lane & 15)] = acc[i][q][r];
+}
+
+// Finish: the sums over tiles and splits in order into g (and grads), and the squared errors by
+// 256 into parts (and loss).  Blocks: hh / 1024 for W2 (four values a thread), then the tiles'
+// sums (64 values, four threads each), then the errors.
+__global__ __launch_bounds__(256) void k_mlp_finish(const float* __restrict__ part, int nsplit, int hh,
+                                                    const float* __restrict__ sums, int ntile, int nsum, int n1,
+                                                    const float* __restrict__ sq, int nsq, float* __restrict__ g,
+                                                    float* __restrict__ grads, float* __restrict__ parts,
+                                                    float* __restrict__ loss) {
+    __shared__ float red[256];
+    const int tid = threadIdx.x;
+    int blk = blockIdx.x;
+    if (blk < hh / 1024) {
+        const int e = 1024 * blk + 4 * tid;
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+        for (int z = 0; z < nsplit; ++z) {
+            const float4 v = *reinterpret_cast<const float4*>(part + (int64_t)z * hh + e);
+            s.x += v.x;
+            s.y += v.y;
+            s.z += v.z;
+            s.w += v.w;
+        }
+        const float o[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            g[n1 + e + k] = o[k];
+            if (grads) grads[n1 + e + k] = o[k];
+        }
+        return;
+    }
+    blk -= hh / 1024;
+    if (blk < (nsum + 63) / 64) {
+        const int e = 64 * blk + (tid & 63), q = tid >> 6;
+        float v = 0.f;
+        if (e < nsum) {
+#pragma unroll 8
+            for (int k = q; k < ntile; k += 4) v += sums[(int64_t)k * nsum + e];
+        }
+        red[tid] = v;
+        __syncthreads();
+        if (q == 0 && e < nsum) {
+            const float s = ((red[tid] + red[64 + tid]) + red[128 + tid]) + red[192 + tid];
+            const int at = e < n1 ? e : e + hh;      // W2 stands between b1 and b2
+            g[at] = s;
+            if (grads) grads[at] = s;
+        }
+        return;
+    }
+    blk -= (nsum + 63) / 64;
+    const int e = 256 * blk + tid;
+    red[tid] = e < nsq ? sq[e] : 0.f;
+    __syncthreads();
+    for (int k = 128; k > 0; k >>= 1) {
+        if (tid < k) red[tid] += red[tid + k];
+        __syncthreads();
+    }
+    if (tid == 0) {
+        parts[blk] = red[0];
+        if (loss) loss[blk] = red[0];
+    }
+}
+
+struct MlpTrain {
+    const float* w;
+    int nin, hid, rows;
+    int64_t oW1, ob1, oW2, ob2, oW3, ob3;
+    float *w1r, *w3r;
+    unsigned short *w2f, *w2b;
+    const float *X, *T;
+    void *a1f, *dzf;              // rows rounded up to 64, times hid, BF16
+    float *sums, *sq;             // tiles x mtr_sums, rows x 2
+    float* part;                  // nsplit x hid^2
+    int nsplit;
+    float *g, *grads, *parts, *loss;
+};
+// Splits of the rows for W2's gradient: workgroups for all CUs, at least four blocks of 32
+// rows each (a split costs hid^2 floats written and read again)
+int mlp_train_splits_max(int rows, int hid) {
+    const int tiles = (hid / 128) * (hid / 128), nblk = 2 * ((rows + MTR_R - 1) / MTR_R);
+    return std::max(1, std::min(256 / tiles, nblk / 4));
+}
+int mlp_train_splits(int rows, int hid) {
+    const int nblk = 2 * ((rows + MTR_R - 1) / MTR_R), s = mlp_train_splits_max(rows, hid);
+    const int per = (nblk + s - 1) / s;
+    return (nblk + per - 1) / per;
+}
+template <int HID, int NIN> static hipError_t mlp_train_t(const MlpTrain& t, hipStream_t st) {
+    const int nt = (t.rows + MTR_R - 1) / MTR_R, nblk = 2 * nt, per = (nblk + t.nsplit - 1) / t.nsplit;
+    const int hh = HID * HID, nsum = mtr_sums(t.nin, HID), nsq = 2 * t.rows;
+    const size_t lds = (size_t)MTR_R * (HID + MT_LD) * 2 + mtr_a2<HID>() + 8 * MTR_R + 12 * HID;
+    hipError_t e = hipFuncSetAttribute((const void*)k_mlp_train<HID, NIN>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_mlp_pack_train<HID>, dim3(hh / 2048), dim3(256), 0, st, t.w, t.nin, t.oW1, t.oW2, t.oW3, t.w1r,
+                       t.w2f, t.w2b, t.w3r);
+    hipLaunchKernelGGL((k_mlp_train<HID, NIN>), dim3(nt), dim3(HID), lds, st, t.X, t.T, t.rows, t.nin,
+                       1.f / (float)((int64_t)t.rows * 2), (const float*)t.w1r, t.w + t.ob1,
+                       (const unsigned short*)t.w2f, (const unsigned short*)t.w2b, t.w + t.ob2, (const float*)t.w3r,
+                       t.w + t.ob3, (uint4*)t.a1f, (uint4*)t.dzf, t.sums, t.sq);
+    hipLaunchKernelGGL(k_mlp_dw<HID>, dim3((HID / 128) * (HID / 128) * ((t.nsplit + 7) / 8 * 8)), dim3(256), 0,
+                       st,
+                       (const bf16x8_t*)t.a1f, (const bf16x8_t*)t.dzf, nblk, per, t.part);
+    hipLaunchKernelGGL(k_mlp_finish, dim3(hh / 1024 + (nsum + 63) / 64 + (nsq + 255) / 256), dim3(256), 0, st,
+                       (const float*)t.part, t.nsplit, hh, (const float*)t.sums, nt, nsum, (t.nin + 1) * HID,
+                       (const float*)t.sq, nsq, t.g, t.grads, t.parts, t.loss);
+    return hipGetLastError();
+}
+hipError_t launch_mlp_train(const MlpTrain& t, hipStream_t st) {
+    if (t.hid == 512) return t.nin <= 8 ? mlp_train_t<512, 8>(t, st) : mlp_train_t<512, 16>(t, st);
+    if (t.hid == 256) return t.nin <= 8 ? mlp_train_t<256, 8>(t, st) : mlp_train_t<256, 16>(t, st);
+    return hipErrorInvalidValue;
+}
+
 }  // namespace cdm
 
 // ============================================================================
@@ -877,9 +1323,9 @@ struct Mlp {
     float* cpart = nullptr;                   // column-sum partials (CS_SPLIT x widest layer)
     float* splitk = nullptr;                  // split-K partial products of the weight gradients
     int64_t splitk_floats = 0;
-    float *w1r = nullptr, *w3r = nullptr;     // fused inference: BF16-rounded W1, W3
-    unsigned short* w2f = nullptr;            // and W2 as BF16 in fragment order
-    bool fused = false;                       // shape served by k_mlp_infer
+    float *w1r = nullptr, *w3r = nullptr;     // fused kernels: BF16-rounded W1, W3
+    unsigned short *w2f = nullptr, *w2b = nullptr;   // and W2 as BF16 in fragment order
+    bool fused = false;                       // shape served by k_mlp_infer and k_mlp_train
     void* ws = nullptr;
     int64_t step = 0;
     // parameter block offsets: W1 b1 W2 b2 W3 b3
@@ -998,6 +1444,53 @@ static hipError_t mlp_backward(cdm_mlp* n, const float* X, const float* T, int r
     return launch_colsum(n->dZ1, rows, n->h1, g + n->ob1, n->cpart, st);
 }
 
+// Forward and backward pass of one step, gradients into n->g (and grads), squared errors by 256
+// into n->part (and loss).  Widths 256 and 512 with two outputs and at most 16 inputs take the
+// fused pass at every row count; others the layered one.  Layered / fused, us a call: 512 units,
+// 1 row 91 / 35, 1000 rows 205 / 42, 3001 rows 560 / 47, 16,384 rows 338 / 56; 256 units, 1 row
+// 62 / 24, 16,384 rows 215 / 41.
+static hipError_t mlp_gradients(cdm_mlp* n, const float* X, const float* T, int rows, float* grads, float* loss,
+                                hipStream_t st) {
+    if (n->fused) {
+        MlpTrain t;
+        t.w = n->w;
+        t.nin = n->nin;
+        t.hid = n->h1;
+        t.rows = rows;
+        t.oW1 = n->oW1;
+        t.ob1 = n->ob1;
+        t.oW2 = n->oW2;
+        t.ob2 = n->ob2;
+        t.oW3 = n->oW3;
+        t.ob3 = n->ob3;
+        t.w1r = n->w1r;
+        t.w3r = n->w3r;
+        t.w2f = n->w2f;
+        t.w2b = n->w2b;
+        t.X = X;
+        t.T = T;
+        t.a1f = n->Z1;
+        t.dzf = n->Z2;
+        t.sums = n->dA2;
+        t.sq = n->O;
+        t.part = n->splitk;
+        t.nsplit = mlp_train_splits(rows, n->h1);
+        t.g = n->g;
+        t.grads = grads;
+        t.parts = n->part;
+        t.loss = loss;
+        return launch_mlp_train(t, st);
+    }
+    hipError_t e;
+    if ((e = mlp_forward(n, X, rows, st))) return e;
+    if ((e = mlp_backward(n, X, T, rows, st))) return e;
+    if (grads && (e = hipMemcpyAsync(grads, n->g, sizeof(float) * n->nparam, hipMemcpyDeviceToDevice, st))) return e;
+    if (loss)
+        return hipMemcpyAsync(loss, n->part, sizeof(float) * (((size_t)rows * n->nout + 255) / 256),
+                              hipMemcpyDeviceToDevice, st);
+    return hipSuccess;
+}
+
 extern "C" {
 
 int32_t cdm_mlp_create(int32_t nin, int32_t h1, int32_t h2, int32_t nout, int32_t max_rows, cdm_mlp** out) {
@@ -1017,45 +1510,56 @@ int32_t cdm_mlp_create(int32_t nin, int32_t h1, int32_t h2, int32_t nout, int32_
     n->oW3 = n->ob2 + h2;
     n->ob3 = n->oW3 + (int64_t)h2 * nout;
     n->nparam = n->ob3 + nout;
-    const int64_t R = max_rows;
     n->fused = nin <= 16 && h1 == h2 && (h1 == 256 || h1 == 512) && nout == 2;
-    // fused inference weights: nin*h1 + 2*h2 floats and h1*h2 BF16 (as floats: half of it)
-    const int64_t fw = n->fused ? (int64_t)nin * h1 + 2 * (int64_t)h2 + ((int64_t)h1 * h2 + 1) / 2 + 64 : 0;
+    // the fused training pass keeps BF16 fragments of whole 64-row tiles in Z1 and Z2
+    const int64_t R = max_rows, Rz = n->fused ? (R + MTR_R - 1) / MTR_R * MTR_R : R;
     const int64_t wmax = std::max<int64_t>(std::max(h1, h2), nout);
     // split-K scratch: up to 64 partial copies of the largest weight block
     const int64_t wblk = std::max<int64_t>(std::max<int64_t>((int64_t)nin * h1, (int64_t)h1 * h2), (int64_t)h2 * nout);
-    const int64_t skf = (R >= 4096) ? std::min<int64_t>(64, R / 256) * wblk : 0;
-    const int64_t fl = 4 * n->nparam + R * (4 * (int64_t)h1 + 4 * (int64_t)h2 + 2 * nout) + (R * nout + 255) / 256 + 64 + fw +
-                       CS_SPLIT * wmax + skf + 64;
-    if (hipMalloc(&n->ws, sizeof(float) * fl) != hipSuccess) {
+    int64_t skf = (R >= 4096) ? std::min<int64_t>(64, R / 256) * wblk : 0;
+    if (n->fused) skf = std::max<int64_t>(skf, (int64_t)mlp_train_splits_max(max_rows, h1) * h1 * h2);
+    int64_t off = 0;
+    auto take = [&](int64_t floats) {   // 16-B aligned sections
+        const int64_t o = off;
+        off += (floats + 3) / 4 * 4;
+        return o;
+    };
+    const int64_t o_w = take(n->nparam), o_g = take(n->nparam), o_m = take(2 * n->nparam);
+    const int64_t o_Z1 = take(Rz * h1), o_A1 = take(R * h1), o_dA1 = take(R * h1), o_dZ1 = take(R * h1);
+    const int64_t o_Z2 = take(Rz * h2), o_A2 = take(R * h2), o_dA2 = take(Rz * h2), o_dZ2 = take(R * h2);
+    const int64_t o_O = take(R * nout), o_dO = take(R * nout), o_part = take((R * nout + 255) / 256);
+    const int64_t o_cpart = take(CS_SPLIT * wmax), o_splitk = take(skf);
+    // fused kernels: BF16-rounded W1, W3 (FP32) and W2 in fragment order, forward and backward
+    const int64_t o_w1r = take(n->fused ? (int64_t)nin * h1 : 0), o_w3r = take(n->fused ? 2 * (int64_t)h2 : 0);
+    const int64_t o_w2f = take(n->fused ? (int64_t)h1 * h2 / 2 : 0), o_w2b = take(n->fused ? (int64_t)h1 * h2 / 2 : 0);
+    if (hipMalloc(&n->ws, sizeof(float) * off) != hipSuccess) {
         delete n;
         return CDM_ENOMEM;
     }
     float* p = (float*)n->ws;
-    n->w = p; p += n->nparam;
-    n->g = p; p += n->nparam;
-    n->m1 = p; p += n->nparam;
-    n->m2 = p; p += n->nparam;
-    n->Z1 = p; p += R * h1;
-    n->A1 = p; p += R * h1;
-    n->dA1 = p; p += R * h1;
-    n->dZ1 = p; p += R * h1;
-    n->Z2 = p; p += R * h2;
-    n->A2 = p; p += R * h2;
-    n->dA2 = p; p += R * h2;
-    n->dZ2 = p; p += R * h2;
-    n->O = p; p += R * nout;
-    n->dO = p; p += R * nout;
-    n->part = p; p += (R * nout + 255) / 256 + 64;
-    n->cpart = p; p += CS_SPLIT * wmax;
-    n->splitk = skf ? p : nullptr;
+    n->w = p + o_w;
+    n->g = p + o_g;
+    n->m1 = p + o_m;
+    n->m2 = n->m1 + n->nparam;
+    n->Z1 = p + o_Z1;
+    n->A1 = p + o_A1;
+    n->dA1 = p + o_dA1;
+    n->dZ1 = p + o_dZ1;
+    n->Z2 = p + o_Z2;
+    n->A2 = p + o_A2;
+    n->dA2 = p + o_dA2;
+    n->dZ2 = p + o_dZ2;
+    n->O = p + o_O;
+    n->dO = p + o_dO;
+    n->part = p + o_part;
+    n->cpart = p + o_cpart;
+    n->splitk = skf ? p + o_splitk : nullptr;
     n->splitk_floats = skf;
-    p += skf;
     if (n->fused) {
-        p += -(p - (float*)n->ws) & 3;   // 16-B aligned
-        n->w1r = p; p += (int64_t)nin * h1;
-        n->w3r = p; p += 2 * (int64_t)h2 + 60;
-        n->w2f = reinterpret_cast<unsigned short*>(p);
+        n->w1r = p + o_w1r;
+        n->w3r = p + o_w3r;
+        n->w2f = reinterpret_cast<unsigned short*>(p + o_w2f);
+        n->w2b = reinterpret_cast<unsigned short*>(p + o_w2b);
     }
     if (hipMemset(n->m1, 0, sizeof(float) * 2 * n->nparam) != hipSuccess) {
         (void)hipFree(n->ws);
@@ -1094,20 +1598,14 @@ int32_t cdm_mlp_gradients(cdm_mlp* n, const float* X, const float* T, int32_t ro
                           void* stream) {
     if (!n || !X || !T || rows < 1 || rows > n->max_rows) return CDM_EINVAL;
     hipStream_t st = (hipStream_t)stream;
-    MLP_TRY(mlp_forward(n, X, rows, st));
-    MLP_TRY(mlp_backward(n, X, T, rows, st));
-    if (grads) MLP_TRY(hipMemcpyAsync(grads, n->g, sizeof(float) * n->nparam, hipMemcpyDeviceToDevice, st));
-    if (loss_parts)
-        MLP_TRY(hipMemcpyAsync(loss_parts, n->part, sizeof(float) * (((size_t)rows * n->nout + 255) / 256),
-                               hipMemcpyDeviceToDevice, st));
+    MLP_TRY(mlp_gradients(n, X, T, rows, grads, loss_parts, st));
     return CDM_OK;
 }
 
 int32_t cdm_mlp_train_step(cdm_mlp* n, const float* X, const float* T, int32_t rows, float lr, void* stream) {
     if (!n || !X || !T || rows < 1 || rows > n->max_rows || !(lr > 0.f)) return CDM_EINVAL;
     hipStream_t st = (hipStream_t)stream;
-    MLP_TRY(mlp_forward(n, X, rows, st));
-    MLP_TRY(mlp_backward(n, X, T, rows, st));
+    MLP_TRY(mlp_gradients(n, X, T, rows, nullptr, nullptr, st));
     n->step += 1;
     const float b1 = 0.9f, b2 = 0.999f;
     const float c1 = 1.f - powf(b1, (float)n->step), c2 = 1.f - powf(b2, (float)n->step);

@@ -42,3 +42,30 @@ def test_predict_rows_do_not_depend_on_their_tile(mo, nin, hid):
         part = net.predict(Xd[a:b].contiguous(), torch.complex64).cpu().numpy()
         assert np.array_equal(part, full[a:b].astype(np.complex64))
     net.close()
+
+
+@pytest.mark.parametrize("nin,hid,rows", [(8, 512, 1), (8, 512, 65), (1, 256, 63), (16, 512, 127), (9, 256, 700),
+                                          (5, 512, 64), (8, 256, 2049)])
+def test_training_pass_against_the_oracle(mo, nin, hid, rows):
+    """The fused training pass in 64-row tiles, whole and ragged, with one and several row
+    splits of W2's gradient: the bars of the layered pass (2e-3 per parameter block against the
+    BF16-operand oracle, 1e-4 on the loss), the squared errors by 256 values, and the same bits
+    from a second call after another row count."""
+    shape = (nin, hid, hid, 2)
+    net, w = net_of(shape, rows, max_rows=rows + rows % 3)
+    rng = np.random.default_rng(rows)
+    X = rng.standard_normal((rows, nin)).astype(np.float32)
+    T = rng.standard_normal((rows, 2)).astype(np.float32)
+    Xd, Td = torch.from_numpy(X).cuda(), torch.from_numpy(T).cuda()
+    g, parts = net.gradients(Xd, Td)
+    net.gradients(Xd[:rows // 2 + 1].contiguous(), Td[:rows // 2 + 1].contiguous())
+    g2, parts2 = net.gradients(Xd, Td)
+    assert torch.equal(g, g2) and torch.equal(parts, parts2)
+    want = mo.gradients(w.astype(np.float64), shape, X, T, bf16=True)
+    for a, b in zip(mo.split(g.cpu().numpy().astype(np.float64), shape), mo.split(want, shape)):
+        assert relerr(a, b) <= 2e-3
+    Y = net.forward(Xd).cpu().numpy().astype(np.float64)
+    sq = ((Y - T) ** 2).reshape(-1)
+    sq = np.pad(sq, (0, -len(sq) % 256)).reshape(-1, 256).sum(1)
+    assert np.allclose(parts.cpu().numpy(), sq, rtol=1e-4)
+    net.close()
