@@ -11,9 +11,9 @@ namespace cdm {
 
 // Tiling of one instance: panels of k users, Up = npan * k, P workgroups of R rows each in
 // the sweep (one workgroup for a single panel of 128), nblk 64 x 64 blocks of the lower
-// triangle over nsplit row splits in the Gram pass.
+// triangle over nwork workgroups in the Gram pass.
 struct GsShape {
-    int k = 0, npan = 0, Up = 0, R = 0, P = 0, nblk = 0, nsplit = 0;
+    int k = 0, npan = 0, Up = 0, R = 0, P = 0, nblk = 0, nwork = 0;
     bool one = false;
 };
 GsShape gs_shape(int B, int U);
@@ -50,10 +50,11 @@ struct GsLaunch {
     int T_max;
     uint64_t timeout_ticks;
     uint32_t* ctr;        // GS_CTR_WORDS words, then the exchange words
-    void* gpart;          // nsplit x nblk x 4096 complex128
+    void* gpart;          // (nwork + nblk) x 4096 complex128
     void* A;              // Up x Up
     void* W;              // Up x Up
     void* M;              // npan x k x k
+    void* Mt;             // and transposed
     void* r;              // B
     void* b;              // Up
     void* xw;             // Up

@@ -9,9 +9,10 @@
 //     b_J <- b_J - W_JK b_K (J != K),   b_K <- -W_KK b_K,   x_K <- x_K + M_K b_K,
 // so the step needs the k values of b_K and nothing of length B: the sweep streams U^2
 // values instead of B U, and one exchange of k values per panel is all that couples the
-// workgroups.  k is 256 instead of the 64 or 128 columns whose tiles of H fit the
-// registers, so a sweep has a quarter of the exchanges.  In exact arithmetic every delta
-// is the sequential sweep's.
+// workgroups.  k is 256 or 512 instead of the 64 or 128 columns whose tiles of H fit the
+// registers, so a sweep has a quarter of the exchanges.  Up to 1024 users one panel holds
+// all, and the deltas follow each other directly, delta <- V delta with V = -M L^H.  In exact
+// arithmetic every delta is the sequential sweep's.
 //
 // Everything here runs in FP64, for complex64 input too: G from FP32 sums would lose
 // digits against the residual form of the sweep, and the FP64 vector and matrix rates of
@@ -19,10 +20,11 @@
 // it is formed anew from H, y and x (two passes over H) after sweeps 2, 8, 40 and 200: the
 // drift of the first, largest steps is gone by then.
 //
-// Stages: k_gs_init, k_gs_gram (64 x 64 blocks of the lower triangle over row splits, on
-// v_mfma_f64_16x16x4_f64), k_gs_assemble (sum of splits, both triangles), k_gs_inv64 and
-// k_gs_mm (the inverse of each D + L by halves, then W), and per segment of sweeps
-// k_gs_rows (r = y - H x), k_gs_grad (b) and the sweep kernel.
+// Stages: k_gs_init, k_gs_gram (64 x 64 blocks of the lower triangle, on
+// v_mfma_f64_16x16x4_f64), k_gs_assemble (sum of their parts, both triangles), k_gs_inv64 and
+// k_gs_mm (the inverse of each D + L by halves, then W or V), and per segment of sweeps
+// k_gs_rows (r = y - H x), k_gs_grad (b) and the sweep kernel: k_gs_one (one workgroup, up to
+// 128 users), k_gs_delta (up to 1024) or k_gs_sweep.
 #include "gs.hpp"
 #include "la_common.hpp"
 
@@ -38,67 +40,81 @@ template <typename V> __device__ __forceinline__ double2 to_d(V v) {
     return make_double2((double)v.x, (double)v.y);
 }
 
-// ---- 64 x 64 complex product tiles on the FP64 matrix cores ------------------------------
-// LDS planes with 32 values of the contraction index per row, contiguous (the pitch of 34
-// keeps fragment reads, 16 rows x 2 values per half-wave, off each other's banks).  Four
-// waves, a quadrant of NB x NB 16 x 16 tiles each: 64 x 64 (NB = 2) for the long Gram
-// sums, 32 x 32 (NB = 1) for the products around the inverse, which have few tiles.
-constexpr int MP = 34, MK = 32;
-template <int NB> struct MmAcc {
-    acc4 r[NB][NB], i[NB][NB];
-    __device__ void zero() {
+// ---- complex product tiles on the FP64 matrix cores -----------------------------------------
+// A wave's 32 x 32 tile (2 x 2 MFMA tiles).  The 16 MFMAs of a step (four values of the
+// contraction index) take 1024 cycles and need four operand loads of 1 KiB, so the operands
+// come straight from memory, D steps ahead in a ring of registers: no LDS, no barrier.
+// Measured against tiles staged through LDS (32 values at a time, two barriers): H^H H of 3000 x
+// 1000 262 -> 220 us (57 TFLOP/s), W of 8192 users 1690 -> 1290 us (60 TFLOP/s).
+typedef double gs_d2 __attribute__((ext_vector_type(2)));
+struct MmAcc {
+    acc4 r[2][2], i[2][2];
+    __device__ __forceinline__ void zero() {
 #pragma unroll
-        for (int a = 0; a < NB; ++a)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
+            for (int b = 0; b < 2; ++b) {
                 r[a][b] = acc4{0.0, 0.0, 0.0, 0.0};
                 i[a][b] = acc4{0.0, 0.0, 0.0, 0.0};
             }
     }
-    // += op(A) B over the staged 32 values; CONJ: op(A) = conj(A)
-    template <bool CONJ> __device__ void step(const double* ar_, const double* ai_, const double* br_,
-                                              const double* bi_, int lane, int wv) {
-        const int qi = wv >> 1, qj = wv & 1;
-#pragma unroll 4
-        for (int k0 = 0; k0 < MK; k0 += 4) {
-            const int rk = k0 + (lane >> 4);
-            double ar[NB], ai[NB], br[NB], bi[NB];
+    // += op(A) B over one step; CONJ: op(A) = conj(A)
+    template <bool CONJ> __device__ __forceinline__ void step(const double2 (&x)[2], const double2 (&y)[2]) {
+        // the two products of an accumulator are kept apart: back to back the second waits
 #pragma unroll
-            for (int a = 0; a < NB; ++a) {
-                const int ra = (16 * NB * qi + 16 * a + (lane & 15)) * MP + rk;
-                const int rb = (16 * NB * qj + 16 * a + (lane & 15)) * MP + rk;
-                ar[a] = ar_[ra];
-                ai[a] = CONJ ? -ai_[ra] : ai_[ra];
-                br[a] = br_[rb];
-                bi[a] = bi_[rb];
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                r[a][b] = mma64(x[a].x, y[b].x, r[a][b]);
+                i[a][b] = mma64(x[a].x, y[b].y, i[a][b]);
             }
-            // the two products of an accumulator are kept apart: back to back the second waits
 #pragma unroll
-            for (int a = 0; a < NB; ++a)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    r[a][b] = mma64(ar[a], br[b], r[a][b]);
-                    i[a][b] = mma64(ar[a], bi[b], i[a][b]);
-                }
+            for (int b = 0; b < 2; ++b) {
+                r[a][b] = mma64(CONJ ? x[a].y : -x[a].y, y[b].y, r[a][b]);
+                i[a][b] = mma64(CONJ ? -x[a].y : x[a].y, y[b].x, i[a][b]);
+            }
+    }
+    // steps s0 .. s1 - 1; fetch(s, x, y): this lane's operands of step s (values of index 4 s +
+    // (lane >> 4): rows lane & 15 of A's two tiles, columns lane & 15 of B's); mask(s, x, y) looks at
+    // them when they are used: in fetch it would wait for the loads
+    template <bool CONJ, typename V, class F, class G>
+    __device__ __forceinline__ void run(int s0, int s1, F fetch, G mask) {
+        constexpr int D = 4;
+        if (s0 >= s1) return;
+        V x[D][2], y[D][2];
+        auto use = [&](int d, int s) __attribute__((always_inline)) {
+            double2 u[2] = {to_d(x[d][0]), to_d(x[d][1])}, v[2] = {to_d(y[d][0]), to_d(y[d][1])};
+            mask(s, u, v);
+            step<CONJ>(u, v);
+        };
 #pragma unroll
-            for (int a = 0; a < NB; ++a)
+        for (int d = 0; d < D; ++d) fetch(min(s0 + d, s1 - 1), x[d], y[d]);
+        int s = s0;
+#pragma unroll 1
+        for (; s + D <= s1; s += D) {
 #pragma unroll
-                for (int b = 0; b < NB; ++b) {
-                    r[a][b] = mma64(-ai[a], bi[b], r[a][b]);
-                    i[a][b] = mma64(ai[a], br[b], i[a][b]);
-                }
+            for (int d = 0; d < D; ++d) {
+                use(d, s + d);
+                __builtin_amdgcn_sched_barrier(0);
+                fetch(min(s + d + D, s1 - 1), x[d], y[d]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
+#pragma unroll
+        for (int d = 0; d < D; ++d)
+            if (s + d < s1) use(d, s + d);
     }
     // f(row, col, value) for this lane's values of the tile
-    template <class F> __device__ void each(int lane, int wv, F f) const {
+    template <class F> __device__ __forceinline__ void each(int lane, F f) const {
 #pragma unroll
-        for (int a = 0; a < NB; ++a)
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+            for (int b = 0; b < 2; ++b)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    f(16 * NB * (wv >> 1) + 16 * a + (lane >> 4) + 4 * e, 16 * NB * (wv & 1) + 16 * b + (lane & 15),
-                      make_double2(r[a][b][e], i[a][b][e]));
+                    f(16 * a + (lane >> 4) + 4 * e, 16 * b + (lane & 15), make_double2(r[a][b][e], i[a][b][e]));
     }
 };
 
@@ -122,59 +138,69 @@ __global__ __launch_bounds__(256) void k_gs_init(const cv<T>* __restrict__ y, co
     for (int k = i; k < nclear; k += gridDim.x * 256) clear[k] = 0;
 }
 
-// One 64 x 64 block (bi, bj) of the lower triangle of H^H H over one split of the rows.
+// The 64 x 64 blocks of the lower triangle of H^H H, a quadrant per wave.  The work, nblk blocks of
+// upb steps of 32 rows, is dealt out evenly: workgroup w takes steps [w n / nw, (w + 1) n / nw)
+// of all n = nblk upb, and leaves its part of block m at place w + m.  Neighbours in this
+// order, which share columns of H, go to one XCD (workgroups go to the 8 XCDs in turn).
+__host__ __device__ inline int64_t gram_first(int w, int64_t n, int nw) { return w * n / nw; }
+__host__ __device__ inline int gram_owner(int64_t step, int64_t n, int nw) {   // the workgroup of a step
+    int w = (int)((step * nw) / n);
+    while (w + 1 < nw && gram_first(w + 1, n, nw) <= step) ++w;
+    while (gram_first(w, n, nw) > step) --w;
+    return w;
+}
 template <typename T>
-__global__ __launch_bounds__(256) void k_gs_gram(const cv<T>* __restrict__ H, int64_t ld, int B, int U,
-                                                 int rows_per_split, double2* __restrict__ gpart, int nblk) {
-    __shared__ double tile[4][64 * MP];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    int bi, bj;
-    lower_block(blockIdx.x, bi, bj);
-    const int r_lo = blockIdx.y * rows_per_split, r_hi = min(B, r_lo + rows_per_split);
-    const bool same = bi == bj;
-    auto fetch = [&](cv<T>(&v)[8], int c0, int r0) {
-        const int row = r0 + (tid & 31);
+__global__ __launch_bounds__(256, 2) void k_gs_gram(const cv<T>* __restrict__ H, int64_t ld, int B, int U, int nblk,
+                                                    double2* __restrict__ gpart) {
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nw = gridDim.x, upb = (B + 31) / 32;
+    const int64_t n = (int64_t)nblk * upb;
+    const int w = nw % 8 == 0 ? (blockIdx.x % 8) * (nw / 8) + blockIdx.x / 8 : blockIdx.x;
+    const int64_t last = gram_first(w + 1, n, nw);
+    for (int64_t at = gram_first(w, n, nw); at < last;) {
+        const int m = (int)(at / upb), u0 = (int)(at % upb), u1 = (int)min((int64_t)upb, u0 + last - at);
+        int bi, bj;
+        lower_block(m, bi, bj);
+        const int ci = bi * 64 + 32 * (wv >> 1) + (lane & 15), cj = bj * 64 + 32 * (wv & 1) + (lane & 15);
+        // columns past U read the last one: their sums are not stored
+        const cv<T>* const pi[2] = {H + (int64_t)min(ci, U - 1) * ld, H + (int64_t)min(ci + 16, U - 1) * ld};
+        const cv<T>* const pj[2] = {H + (int64_t)min(cj, U - 1) * ld, H + (int64_t)min(cj + 16, U - 1) * ld};
+        MmAcc acc;
+        acc.zero();
+        const int whole = min(8 * u1, B / 4), end = min(8 * u1, (B + 3) / 4);
+        auto fetch = [&](int s, cv<T>(&x)[2], cv<T>(&y)[2]) __attribute__((always_inline)) {
+            const int row = 4 * s + (lane >> 4);
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int col = c0 + (tid >> 5) + 8 * k;
-            v[k] = (row < r_hi && col < U) ? H[(int64_t)col * ld + row] : czero<T>();
-        }
-    };
-    auto put = [&](const cv<T>(&v)[8], double* tr, double* ti) {
+            for (int a = 0; a < 2; ++a) {
+                x[a] = pi[a][row];
+                y[a] = pj[a][row];
+            }
+        };
+        acc.template run<true, cv<T>>(8 * u0, whole, fetch, [](int, double2(&)[2], double2(&)[2]) {});
+        if (whole < end) {   // the last rows, fewer than four
+            const int row = 4 * whole + (lane >> 4);
+            double2 x[2], y[2];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int o = ((tid >> 5) + 8 * k) * MP + (tid & 31);
-            tr[o] = v[k].x;
-            ti[o] = v[k].y;
+            for (int a = 0; a < 2; ++a) {
+                x[a] = row < B ? to_d(pi[a][row]) : make_double2(0.0, 0.0);
+                y[a] = row < B ? to_d(pj[a][row]) : make_double2(0.0, 0.0);
+            }
+            acc.template step<true>(x, y);
         }
-    };
-    MmAcc<2> acc;
-    acc.zero();
-    cv<T> va[8], vb[8];
-    if (r_lo < r_hi) {
-        fetch(va, bi * 64, r_lo);
-        if (!same) fetch(vb, bj * 64, r_lo);
+        double2* out = gpart + ((int64_t)w + m) * 4096 + 32 * (wv >> 1) * 64 + 32 * (wv & 1);
+        const int ui = bi * 64 + 32 * (wv >> 1), uj = bj * 64 + 32 * (wv & 1);
+        acc.each(lane, [&](int i, int j, double2 z) {
+            out[i * 64 + j] = (ui + i < U && uj + j < U) ? z : make_double2(0.0, 0.0);
+        });
+        at += u1 - u0;
     }
-    for (int r0 = r_lo; r0 < r_hi; r0 += MK) {
-        put(va, tile[0], tile[1]);
-        if (!same) put(vb, tile[2], tile[3]);
-        __syncthreads();
-        if (r0 + MK < r_hi) {   // in flight during this step's products
-            fetch(va, bi * 64, r0 + MK);
-            if (!same) fetch(vb, bj * 64, r0 + MK);
-        }
-        acc.template step<true>(tile[0], tile[1], same ? tile[0] : tile[2], same ? tile[1] : tile[3], lane, wv);
-        __syncthreads();
-    }
-    double2* out = gpart + ((int64_t)blockIdx.y * nblk + blockIdx.x) * 4096;
-    acc.each(lane, wv, [&](int u, int v, double2 z) { out[u * 64 + v] = z; });
 }
 
-// A (Up x Up, row-major) = the sum of the splits in a fixed order, both triangles (the
+// A (Up x Up, row-major) = the sum of a block's parts in a fixed order, both triangles (the
 // upper as the conjugate of the lower), zero past U.  A workgroup takes 16 rows of a block,
-// a thread four of their elements with the loads of four splits in flight.
-__global__ __launch_bounds__(256) void k_gs_assemble(const double2* __restrict__ gpart, int nsplit, int nblk, int Up,
-                                                     double2* __restrict__ A) {
+// a thread four of their elements with the loads of four parts in flight.
+__global__ __launch_bounds__(256) void k_gs_assemble(const double2* __restrict__ gpart, int nw, int upb, int nblk,
+                                                     int Up, double2* __restrict__ A) {
     __shared__ double2 t[16][65];
     int bi, bj;
     lower_block(blockIdx.x, bi, bj);
@@ -183,15 +209,16 @@ __global__ __launch_bounds__(256) void k_gs_assemble(const double2* __restrict__
 #pragma unroll
     for (int m = 0; m < 4; ++m) s[m] = make_double2(0.0, 0.0);
     if ((int)blockIdx.x < nblk) {   // blocks past the last one that holds users are zero
-        const double2* p = gpart + (int64_t)blockIdx.x * 4096 + i0 * 64 + threadIdx.x;
-        const int64_t step = (int64_t)nblk * 4096;
+        const int64_t n = (int64_t)nblk * upb, first = (int64_t)blockIdx.x * upb;
+        const int w0 = gram_owner(first, n, nw), parts = gram_owner(first + upb - 1, n, nw) - w0 + 1;
+        const double2* p = gpart + ((int64_t)w0 + blockIdx.x) * 4096 + i0 * 64 + threadIdx.x;
         int k = 0;
-        for (; k + 3 < nsplit; k += 4) {
+        for (; k + 3 < parts; k += 4) {
             double2 v[4][4];
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int m = 0; m < 4; ++m) v[q][m] = p[(k + q) * step + 256 * m];
+                for (int m = 0; m < 4; ++m) v[q][m] = p[(int64_t)(k + q) * 4096 + 256 * m];
 #pragma unroll
             for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -200,10 +227,10 @@ __global__ __launch_bounds__(256) void k_gs_assemble(const double2* __restrict__
                     s[m].y += v[q][m].y;
                 }
         }
-        for (; k < nsplit; ++k) {
+        for (; k < parts; ++k) {
             double2 v[4];
 #pragma unroll
-            for (int m = 0; m < 4; ++m) v[m] = p[k * step + 256 * m];
+            for (int m = 0; m < 4; ++m) v[m] = p[(int64_t)k * 4096 + 256 * m];
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
                 s[m].x += v[m].x;
@@ -229,15 +256,17 @@ __global__ __launch_bounds__(256) void k_gs_assemble(const double2* __restrict__
     }
 }
 
-// The inverse of one 64 x 64 diagonal block of D + L, into M (panels of k x k, row-major),
-// with the zeros right of it.  Bound by latency (a few workgroups): the four 16 x 16
-// diagonal blocks by substitution, a wave each and a lane per column, then the blocks below
-// them a diagonal at a time, X_ij = -X_ii sum_k L_ik X_kj, on the matrix cores.
+// The inverse of one 64 x 64 diagonal block of D + L, into M (panels of k x k, row-major) with the
+// zeros right of it, and into Mt, its transpose (no zeros: nothing reads them).  Bound by
+// latency (a few workgroups): the four 16 x 16 diagonal blocks by substitution, a wave each and
+// a lane per column, then the blocks below them a diagonal at a time, X_ij = -X_ii sum_k L_ik
+// X_kj, on the matrix cores.
 // Inactive coordinates (||h_u||^2 + lambda == 0) get zero rows.
 constexpr int IP = 66;   // pitch of the LDS planes
 constexpr size_t GS_INV_LDS = (size_t)4 * 64 * IP * 8;
 __global__ __launch_bounds__(256) void k_gs_inv64(const double2* __restrict__ A, int Up, int U, int k, double lambda,
-                                                  double2* __restrict__ M, uint32_t* __restrict__ status) {
+                                                  double2* __restrict__ M, double2* __restrict__ Mt,
+                                                  uint32_t* __restrict__ status) {
     extern __shared__ __attribute__((aligned(16))) double inv_s[];
     double* Lr = inv_s;
     double* Li = Lr + 64 * IP;
@@ -246,6 +275,14 @@ __global__ __launch_bounds__(256) void k_gs_inv64(const double2* __restrict__ A,
     __shared__ double rd[64];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int u0 = blockIdx.x * 64;
+    const int K = u0 / k, c0 = u0 % k;
+    double2* Mk = M + (int64_t)K * k * k + (int64_t)c0 * k;
+    if (blockIdx.y > 0) {   // the zeros right of the block, beside its inverse
+        const int rest = k - c0 - 64;
+        for (int e = (blockIdx.y - 1) * 256 + tid; e < 64 * rest; e += 256 * (gridDim.y - 1))
+            Mk[(int64_t)(e / rest) * k + c0 + 64 + e % rest] = make_double2(0.0, 0.0);
+        return;
+    }
     double2 av[16];
 #pragma unroll
     for (int m = 0; m < 16; ++m) av[m] = A[(int64_t)(u0 + (tid >> 6) + 4 * m) * Up + u0 + (tid & 63)];
@@ -331,14 +368,12 @@ __global__ __launch_bounds__(256) void k_gs_inv64(const double2* __restrict__ A,
         }
         __syncthreads();
     }
-    const int K = u0 / k, c0 = u0 % k;
-    double2* Mk = M + (int64_t)K * k * k + (int64_t)c0 * k;
-    for (int e = tid; e < 4096; e += 256)
-        Mk[(int64_t)(e >> 6) * k + c0 + (e & 63)] =
-            make_double2(Xr[(e >> 6) * IP + (e & 63)], Xi[(e >> 6) * IP + (e & 63)]);
-    const int rest = k - c0 - 64;
-    for (int e = tid; e < 64 * rest; e += 256)
-        Mk[(int64_t)(e / rest) * k + c0 + 64 + e % rest] = make_double2(0.0, 0.0);
+    double2* const Mtk = Mt + (Mk - M);
+    for (int e = tid; e < 4096; e += 256) {
+        const int i = e >> 6, j = e & 63;
+        Mk[(int64_t)i * k + c0 + j] = make_double2(Xr[i * IP + j], Xi[i * IP + j]);
+        Mtk[(int64_t)i * k + c0 + j] = make_double2(Xr[j * IP + i], Xi[j * IP + i]);
+    }
 }
 
 // 32 x 32 tiles of the products around the inverse:
@@ -346,18 +381,27 @@ __global__ __launch_bounds__(256) void k_gs_inv64(const double2* __restrict__ A,
 //            inverse from its two s x s halves (T in W's space, which is not yet in use);
 //   FOLD     W_JK = G_JK M_K, for J in K's panel L^H M_K (strictly upper triangle of G_KK);
 //   FOLD_V   V = -M L^H for a single panel (the iteration on delta itself).
+// Tiles of users past U are zero.  A workgroup makes one tile, its four waves a quarter of the
+// contraction index each: tiles are few, and one alone is bound by its chain of MFMAs.  FOLD has
+// enough of them: there a workgroup makes 64 x 64, a tile per wave.
 enum { MM_MERGE_T = 0, MM_MERGE_X = 1, MM_FOLD = 2, MM_FOLD_V = 3 };
 template <int MODE>
-__global__ __launch_bounds__(256) void k_gs_mm(const double2* __restrict__ A, double2* __restrict__ M,
-                                               double2* __restrict__ W, int Up, int k, int s) {
-    __shared__ double tile[4][32 * MP];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+__global__ __launch_bounds__(256, 2) void k_gs_mm(const double2* __restrict__ A, double2* __restrict__ M,
+                                                  double2* __restrict__ Mt, double2* __restrict__ W, int Up, int U,
+                                                  int k, int s) {
+    // the left operand lies with the contraction index outermost too (lanes over rows: 256 B a
+    // piece): G is its own conjugate transpose, and M is kept transposed as well
+    constexpr bool HERM = MODE == MM_MERGE_T || MODE == MM_FOLD;
+    __shared__ double red[MODE == MM_FOLD ? 1 : 3][32][64];
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kb = k / 32;
     const int64_t kk = (int64_t)k * k;
     const double2 *a, *b;
-    double2* c;
+    double2 *c, *ct = nullptr;
     int64_t lda, ldb, ldc;
-    int c_lo, c_hi, tri = -1;        // tri: the chunk whose diagonal tile counts strictly above the diagonal only
+    // contraction range in tiles of 32; diag: values of index <= row (FOLD) or >= column (FOLD_V)
+    // relative to these belong to the other triangle and count as zero
+    int c_lo, c_hi, diag = -(1 << 30);
     double sign = 1.0;
     if (MODE == MM_MERGE_T || MODE == MM_MERGE_X) {
         const int sb = s / 32;
@@ -369,28 +413,36 @@ __global__ __launch_bounds__(256) void k_gs_mm(const double2* __restrict__ A, do
         const int q = n % (kb / (2 * sb)), p = n / (kb / (2 * sb));
         const int lo = 2 * q * s, hi = lo + s;
         const int64_t pm = p * kk;
+        const bool live = p * k + hi + 32 * i < U;
         if (MODE == MM_MERGE_T) {
-            a = A + (int64_t)(p * k + hi + 32 * i) * Up + p * k + lo;
+            a = A + (int64_t)(p * k + lo) * Up + p * k + hi + 32 * i;
             lda = Up;
             b = M + pm + (int64_t)lo * k + lo + 32 * j;
             c = W + pm + (int64_t)(hi + 32 * i) * k + lo + 32 * j;
             c_lo = j;
-            c_hi = sb;
+            c_hi = live ? sb : j;
         } else {
-            a = M + pm + (int64_t)(hi + 32 * i) * k + hi;
+            a = Mt + pm + (int64_t)hi * k + hi + 32 * i;
             lda = k;
             b = W + pm + (int64_t)hi * k + lo + 32 * j;
             c = M + pm + (int64_t)(hi + 32 * i) * k + lo + 32 * j;
+            ct = Mt + pm + (int64_t)(lo + 32 * j) * k + hi + 32 * i;
             c_lo = 0;
-            c_hi = i + 1;
+            c_hi = live ? i + 1 : 0;
             sign = -1.0;
         }
         ldb = ldc = k;
     } else if (MODE == MM_FOLD) {
-        const int nb = Up / 32;
-        const int J = blockIdx.x % nb, j = blockIdx.x / nb;   // row block, column block of W
-        const int K = j / kb, jl = j % kb, Jl = J - K * kb;
-        a = A + (int64_t)J * 32 * Up + K * k;
+        // The column blocks of one row block and panel go to one XCD, which reads G_JK once.  Their
+        // order rotates from one to the next: workgroups go to an XCD's four shader engines in
+        // turn and these wait for each other, so one that always drew the longest sums would hold
+        // up all (8192 users: 1860 us, rotated 1290).
+        const int nb = Up / 64, x = blockIdx.x % 8, m = blockIdx.x / 8;
+        const int jk = (m / (kb / 2)) * 8 + x, jr = (m + m / (kb / 2)) % (kb / 2);
+        if (jk >= nb * (Up / k)) return;   // the grid is a multiple of 8
+        const int J = 2 * (jk % nb) + (wv >> 1), K = jk / nb, jl = 2 * jr + (wv & 1);
+        const int j = K * kb + jl, Jl = J - K * kb;
+        a = A + (int64_t)K * k * Up + J * 32;
         lda = Up;
         b = M + K * kk + 32 * jl;
         ldb = k;
@@ -400,57 +452,79 @@ __global__ __launch_bounds__(256) void k_gs_mm(const double2* __restrict__ A, do
         c_hi = kb;
         if (Jl >= 0 && Jl < kb) {
             c_lo = max(jl, Jl);
-            tri = Jl;
+            diag = 32 * Jl;
         }
     } else {
-        const int j = blockIdx.x % kb, i = blockIdx.x / kb;
-        a = M + (int64_t)i * 32 * k;
+        // shells of equal min(i, j), the longest sums first; every other 256 (one per CU) backwards
+        int n = blockIdx.x;
+        if ((n >> 8) & 1) n ^= 255;
+        int m = (int)sqrtf((float)n);
+        while (m * m > n) --m;
+        while ((m + 1) * (m + 1) <= n) ++m;
+        const int o = n - m * m, c0 = kb - 1 - m;
+        const int i = c0 + max(0, o - m), j = c0 + (o <= m ? o : 0);
+        a = Mt + 32 * i;
         lda = k;
         b = A + 32 * j;
         ldb = Up;
         c = W + (int64_t)i * 32 * k + j * 32;
         ldc = k;
         c_lo = 0;
-        c_hi = min(i, j) + 1;
-        tri = j;
+        c_hi = 32 * max(i, j) < U ? min(i, j) + 1 : 0;
+        diag = 32 * j;
         sign = -1.0;
     }
-    double2 va[4], vb[4];
-    const int i_ = tid >> 5, q_ = tid & 31;
-    auto fetch = [&](int ch) {   // chunk ch: 32 values of the contraction index
+    const int n4 = 8 * (c_hi - c_lo);   // steps, a quarter per wave
+    const int s0 = 8 * c_lo + (MODE == MM_FOLD ? 0 : n4 * wv / 4);
+    const int s1 = MODE == MM_FOLD ? 8 * c_hi : 8 * c_lo + n4 * (wv + 1) / 4;
+    const int l16 = lane & 15, g = lane >> 4;
+    MmAcc acc;
+    acc.zero();
+    auto fetch = [&](int st, double2(&x)[2], double2(&y)[2]) __attribute__((always_inline)) {
+        const int q = 4 * st + g;
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            va[m] = a[(int64_t)(i_ + 8 * m) * lda + 32 * ch + q_];
-            vb[m] = b[(int64_t)(32 * ch + i_ + 8 * m) * ldb + q_];
-        }
-        if ((MODE == MM_FOLD || MODE == MM_FOLD_V) && ch == tri) {
-#pragma unroll
-            for (int m = 0; m < 4; ++m)
-                if (q_ <= i_ + 8 * m) {
-                    if (MODE == MM_FOLD) va[m] = make_double2(0.0, 0.0);
-                    else vb[m] = make_double2(0.0, 0.0);
-                }
+        for (int t = 0; t < 2; ++t) {
+            x[t] = a[(int64_t)q * lda + l16 + 16 * t];
+            y[t] = b[(int64_t)q * ldb + l16 + 16 * t];
         }
     };
-    MmAcc<1> acc;
-    acc.zero();
-    if (c_lo < c_hi) fetch(c_lo);
-    for (int ch = c_lo; ch < c_hi; ++ch) {
+    auto mask = [&](int st, double2(&x)[2], double2(&y)[2]) __attribute__((always_inline)) {
+        const int q = 4 * st + g - diag - l16;
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            const int oa = (i_ + 8 * m) * MP + q_, ob = q_ * MP + i_ + 8 * m;
-            tile[0][oa] = va[m].x;
-            tile[1][oa] = va[m].y;
-            tile[2][ob] = vb[m].x;
-            tile[3][ob] = vb[m].y;
+        for (int t = 0; t < 2; ++t) {
+            if (MODE == MM_FOLD && q <= 16 * t) x[t] = make_double2(0.0, 0.0);
+            if (MODE == MM_FOLD_V && q >= 16 * t) y[t] = make_double2(0.0, 0.0);
         }
-        __syncthreads();
-        if (ch + 1 < c_hi) fetch(ch + 1);
-        acc.template step<false>(tile[0], tile[1], tile[2], tile[3], lane, wv);
-        __syncthreads();
+    };
+    acc.template run<HERM, double2>(s0, s1, fetch, mask);
+    if (MODE == MM_FOLD) {
+        acc.each(lane, [&](int i, int j, double2 z) { c[(int64_t)i * ldc + j] = z; });
+        return;
     }
-    acc.each(lane, wv, [&](int i, int j, double2 z) {
-        c[(int64_t)i * ldc + j] = make_double2(sign * z.x, sign * z.y);
+    if (wv > 0) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                red[wv - 1][8 * t + e][lane] = acc.r[t >> 1][t & 1][e];
+                red[wv - 1][8 * t + 4 + e][lane] = acc.i[t >> 1][t & 1][e];
+            }
+    }
+    __syncthreads();
+    if (wv > 0) return;
+#pragma unroll
+    for (int w = 0; w < 3; ++w)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                acc.r[t >> 1][t & 1][e] += red[w][8 * t + e][lane];
+                acc.i[t >> 1][t & 1][e] += red[w][8 * t + 4 + e][lane];
+            }
+    acc.each(lane, [&](int i, int j, double2 z) {
+        const double2 v = make_double2(sign * z.x, sign * z.y);
+        c[(int64_t)i * ldc + j] = v;
+        if (MODE == MM_MERGE_X) ct[(int64_t)j * k + i] = v;
     });
 }
 
@@ -913,31 +987,172 @@ __global__ __launch_bounds__(1024) void k_gs_finish(const double2* __restrict__ 
         if (e_ != hipSuccess) return e_;    \
     } while (0)
 
+// Sweeps t0 + 1 .. t1 of a single panel of 129 to 1024 users over several workgroups
+// (cooperative launch): delta <- V delta, V = -M L^H, with V in the registers of the chip (16 MiB at
+// 1024 users), so a sweep moves nothing but one exchange of k deltas.  Workgroup w owns R rows of
+// V; eight tile waves take R / 8 of them, a lane per column modulo 64.  The other GS_CW waves
+// gather every delta (tagged words, one memory round trip) into LDS behind one barrier, and
+// each workgroup keeps all of x in theirs: its norms, and with them the decision to stop, are the
+// same bits everywhere and need no exchange.  They are formed while the tile waves work and
+// looked at a sweep later, before x moves on.
+// Bound by the exchange: 3000 x 1000 complex128, 39 sweeps, 4.0 us each (two panels of 512 with M and W
+// streamed: 8.4), the whole solve 850 -> 700 us.
+template <int R, int KC>
+__global__ __launch_bounds__(64 * (8 + GS_CW), 1) void k_gs_delta(GsSweepArgs a, int t0, int t1) {
+    constexpr int NW = 8, RW = R / NW, k = 64 * KC, GC = KC / GS_CW;
+    if (*a.done) return;
+    __shared__ double2 ds[2][k];
+    __shared__ double2 st[2][GS_CW];
+    __shared__ int go[2][GS_CW];
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = blockIdx.x;
+    const bool comm = wid >= NW;
+    const int row0 = w * R + (comm ? 0 : wid * RW), i0 = (wid - NW) * 64 * GC + lane;
+    double2 V[RW][KC], v[GC], x[GC];
+    auto product = [&](auto row, auto in, double2(&d)[RW]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < RW; ++r) d[r] = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int q = 0; q < KC; ++q) {
+            const double2 z = in(q);
+#pragma unroll
+            for (int r = 0; r < RW; ++r) cfma(d[r], row(r, q), z);
+        }
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            d[r].x = group_sum<1>(d[r].x);
+            d[r].y = group_sum<1>(d[r].y);
+        }
+    };
+    auto publish = [&](const double2(&d)[RW], int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+            if (lane == r) gs_put(a.xch + (int64_t)(t & 1) * k * 3, k, row0 + r, d[r], (uint32_t)t);
+    };
+    if (!comm) {
+        double2 d[RW];   // the first delta is M b
+        product([&](int r, int q) { return a.M[(int64_t)(row0 + r) * k + lane + 64 * q]; },
+                [&](int q) { return a.b[lane + 64 * q]; }, d);
+        publish(d, t0 + 1);
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            const double2* const p = a.W + (int64_t)(row0 + r) * k;   // scalar base, one offset register
+            uint32_t o = (uint32_t)lane;
+            asm("" : "+v"(o));
+#pragma unroll
+            for (int q = 0; q < KC; ++q) V[r][q] = p[o + 64 * q];
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < GC; ++q) x[q] = a.x[i0 + 64 * q];
+    }
+    double S = 0.0, X = 0.0;
+    // S, X and the decision of the sweep whose parts lie in st[p]
+    auto met = [&](int p) __attribute__((always_inline)) {
+        S = X = 0.0;
+#pragma unroll
+        for (int q = 0; q < GS_CW; ++q) {
+            S += st[p][q].x;
+            X += st[p][q].y;
+        }
+        return a.tol > 0.0 && !(S > 2.0 * a.tol * a.tol * X) && sqrt(S) <= a.tol * sqrt(X);
+    };
+    int code = 1, t = t0 + 1, par = 0;   // code: 1 goes on, 2 met, 3 given up
+    for (;; ++t, par ^= 1) {
+        if (comm) {
+            int g = 1;
+            uint64_t tw = 0;
+            bool ok = false;
+            for (;;) {
+                if (!ok) {
+                    ok = true;
+#pragma unroll
+                    for (int q = 0; q < GC; ++q)
+                        ok &= gs_get(a.xch + (int64_t)(t & 1) * k * 3, k, i0 + 64 * q, (uint32_t)t, v[q]);
+                }
+                if (__all(ok)) break;
+                const uint64_t now = wall_clock64();   // bounded: given up after the time limit, or with the others
+                if (!tw) tw = now;
+                if (ld_relaxed(a.abort_flag) || now - tw > a.timeout_ticks) {
+                    if (lane == 0) st_relaxed(a.abort_flag, 1u);
+                    g = 3;
+                    break;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < GC; ++q) ds[par][i0 + 64 * q] = v[q];
+            if (lane == 0) go[par][wid - NW] = g;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < GS_CW; ++q) code = max(code, go[par][q]);
+        if (code == 3) break;
+        if (!comm && t < t1) {
+            double2 d[RW];
+            product([&](int r, int q) { return V[r][q]; }, [&](int q) { return ds[par][lane + 64 * q]; }, d);
+            publish(d, t + 1);
+        }
+        if (a.tol > 0.0 && t - 1 > t0 && met(par ^ 1)) {
+            code = 2;
+            break;
+        }
+        if (comm) {
+            double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+            for (int q = 0; q < GC; ++q) {
+                x[q].x += v[q].x;
+                x[q].y += v[q].y;
+                s1 += cabs2d(v[q]);
+                s2 += cabs2d(x[q]);
+            }
+            s1 = group_sum<1>(s1);
+            s2 = group_sum<1>(s2);
+            if (lane == 0) st[par][wid - NW] = make_double2(s1, s2);
+        }
+        if (t == t1) break;
+    }
+    bool stop = code != 1;
+    if (code == 1) {
+        __syncthreads();
+        stop = met(par);
+    }
+    if (w != 0 || !comm) return;
+#pragma unroll
+    for (int q = 0; q < GC; ++q) a.x[i0 + 64 * q] = x[q];
+    if (wid == NW && lane == 0) {
+        gs_info(a.info, code == 1 ? t : t - 1, S, X, a.tol, code != 3);
+        if (stop) *a.done = 1;
+    }
+}
+
+constexpr int GS_DELTA_R = 8;   // rows per workgroup of k_gs_delta
+
 GsShape gs_shape(int B, int U) {
     GsShape s;
-    // panels as wide as the LDS holds R rows of M (128 KB): one exchange per panel and sweep.
-    // R = 16 rows a workgroup up to 4096 users (fewer workgroups poll fewer copies of the same
-    // words: 3000 x 1000, 39 sweeps, 16 rows 818 us, 8 rows 905 us; 256-column panels 1031 us),
-    // 32 above, so that at most 256 workgroups take part
-    s.k = U <= 128 ? 128 : (U <= 256 || U > 4096 ? 256 : 512);
+    // Up to 1024 users one panel, V in registers (R = 8: 16 rows of 1024 spill, 773 against 691 us
+    // for 3000 x 1000 and 40 sweeps; up to 512 users both alike).  Above, panels as wide as the
+    // LDS holds R rows of M (128 KB): one exchange per panel and sweep; R = 16 rows a workgroup
+    // up to 4096 users (fewer workgroups poll fewer copies of the same words: 3000 x 1000 on two
+    // panels, 39 sweeps, 16 rows 818 us, 8 rows 905 us; 256-column panels 1031 us), 32 above, so
+    // that at most 256 workgroups take part
+    s.k = U <= 128 ? 128 : (U <= 256 || U > 4096 ? 256 : (U <= 512 || U > 1024 ? 512 : 1024));
     s.npan = (U + s.k - 1) / s.k;
     s.Up = s.npan * s.k;
     s.one = U <= 128;
-    s.R = s.one ? 128 : (U > 4096 ? 32 : 16);
+    s.R = s.one ? 128 : (s.npan == 1 ? GS_DELTA_R : (U > 4096 ? 32 : 16));
     s.P = s.Up / s.R;
     s.nblk = ((U + 63) / 64) * ((U + 63) / 64 + 1) / 2;
-    // splits of the rows: fewest rounds of resident workgroups (two per CU) for the work of
-    // a split (about 10 us per 32 rows at the full rate) and its partial block
+    // workgroups of the Gram pass: two per CU, fewer where the parts of blocks that they leave
+    // (64 KiB each) would cost more than the shorter runs of steps gain.  Us: a step 4.4 (two on a
+    // CU 7.6), a part 0.045
+    const int64_t n = (int64_t)s.nblk * ((B + 31) / 32);
     double best = 0.0;
-    s.nsplit = 1;
-    for (int ns = 1; ns <= 32; ++ns) {
-        const int steps = (B + 32 * ns - 1) / (32 * ns);
-        if (ns > 1 && steps < 1) break;
-        const double rounds = (double)((s.nblk * ns + 511) / 512);
-        const double cost = rounds * (steps * 10.0 + 5.0) + (double)s.nblk * ns * 0.045;
-        if (ns == 1 || cost < best) {
+    s.nwork = 1;
+    for (int nw = 1; nw <= 512 && nw <= n; nw += nw < 16 ? 1 : 8) {
+        const double cost = (double)((n + nw - 1) / nw) * (nw > 256 ? 7.6 : 4.4) + 0.045 * (nw + s.nblk);
+        if (nw == 1 || cost < best) {
             best = cost;
-            s.nsplit = ns;
+            s.nwork = nw;
         }
     }
     return s;
@@ -949,11 +1164,20 @@ size_t gs_exchange_words(const GsShape& s) {
 
 // the sweep kernel of a tiling: its R and k are the kernel's own (NULL: none is built)
 static const void* gs_sweep_fn(const GsShape& s) {
-    if (s.k == 256 && s.R == 16) return (const void*)k_gs_sweep<16, 8, 4>;
+    if (s.npan == 1) {
+        if (s.R != GS_DELTA_R) return nullptr;
+        if (s.k == 256) return (const void*)k_gs_delta<GS_DELTA_R, 4>;
+        if (s.k == 512) return (const void*)k_gs_delta<GS_DELTA_R, 8>;
+        if (s.k == 1024) return (const void*)k_gs_delta<GS_DELTA_R, 16>;
+        return nullptr;
+    }
     if (s.k == 512 && s.R == 16) return (const void*)k_gs_sweep<16, 8, 8>;
     if (s.k == 256 && s.R == 32) return (const void*)k_gs_sweep<32, 8, 4>;
     return nullptr;
 }
+
+// dynamic LDS of the sweep kernel: the workgroup's rows of M (several panels)
+static size_t gs_sweep_lds(const GsShape& s) { return s.npan == 1 ? 0 : (size_t)16 * s.R * s.k; }
 
 template <typename T> static hipError_t launch_gs_t(const GsLaunch& L, hipStream_t st) {
     const GsShape& s = L.s;
@@ -961,6 +1185,7 @@ template <typename T> static hipError_t launch_gs_t(const GsLaunch& L, hipStream
     const cv<T>* y = (const cv<T>*)L.y;
     double2* A = (double2*)L.A;
     double2* M = (double2*)L.M;
+    double2* Mt = (double2*)L.Mt;
     double2* W = (double2*)L.W;
     double2* r = (double2*)L.r;
     double2* b = (double2*)L.b;
@@ -974,24 +1199,24 @@ template <typename T> static hipError_t launch_gs_t(const GsLaunch& L, hipStream
     if (L.sp) {
         GS_TRY(gs_sparse_matrix(L, st));
     } else {
-        int rps = (L.B + s.nsplit - 1) / s.nsplit;
-        rps = (rps + MK - 1) / MK * MK;
-        hipLaunchKernelGGL(k_gs_gram<T>, dim3(s.nblk, s.nsplit), dim3(256), 0, st, H, L.ld, L.B, L.U, rps,
-                           (double2*)L.gpart, s.nblk);
+        hipLaunchKernelGGL(k_gs_gram<T>, dim3(s.nwork), dim3(256), 0, st, H, L.ld, L.B, L.U, s.nblk,
+                           (double2*)L.gpart);
         hipLaunchKernelGGL(k_gs_assemble, dim3(nb * (nb + 1) / 2, 4), dim3(256), 0, st, (const double2*)L.gpart,
-                           s.nsplit, s.nblk, s.Up, A);
+                           s.nwork, (L.B + 31) / 32, s.nblk, s.Up, A);
     }
-    hipLaunchKernelGGL(k_gs_inv64, dim3(nb), dim3(256), GS_INV_LDS, st, A, s.Up, L.U, s.k, L.lambda, M, L.ctr + 3);
+    hipLaunchKernelGGL(k_gs_inv64, dim3(nb, 1 + s.k / 128), dim3(256), GS_INV_LDS, st, A, s.Up, L.U, s.k, L.lambda, M,
+                       Mt, L.ctr + 3);
     GS_TRY(hipGetLastError());
     for (int h = 64; h < s.k; h *= 2) {
         const int blocks = s.npan * (s.k / (2 * h)) * (h / 32) * (h / 32);
-        hipLaunchKernelGGL(k_gs_mm<MM_MERGE_T>, dim3(blocks), dim3(256), 0, st, A, M, W, s.Up, s.k, h);
-        hipLaunchKernelGGL(k_gs_mm<MM_MERGE_X>, dim3(blocks), dim3(256), 0, st, A, M, W, s.Up, s.k, h);
+        hipLaunchKernelGGL(k_gs_mm<MM_MERGE_T>, dim3(blocks), dim3(256), 0, st, A, M, Mt, W, s.Up, L.U, s.k, h);
+        hipLaunchKernelGGL(k_gs_mm<MM_MERGE_X>, dim3(blocks), dim3(256), 0, st, A, M, Mt, W, s.Up, L.U, s.k, h);
     }
-    if (s.one)
-        hipLaunchKernelGGL(k_gs_mm<MM_FOLD_V>, dim3(4 * nb * nb), dim3(256), 0, st, A, M, W, s.Up, s.k, 0);
+    if (s.npan == 1)
+        hipLaunchKernelGGL(k_gs_mm<MM_FOLD_V>, dim3(4 * nb * nb), dim3(256), 0, st, A, M, Mt, W, s.Up, L.U, s.k, 0);
     else
-        hipLaunchKernelGGL(k_gs_mm<MM_FOLD>, dim3(4 * nb * nb), dim3(256), 0, st, A, M, W, s.Up, s.k, 0);
+        hipLaunchKernelGGL(k_gs_mm<MM_FOLD>, dim3(8 * ((nb * s.npan + 7) / 8) * (s.k / 64)), dim3(256), 0, st, A, M, Mt,
+                           W, s.Up, L.U, s.k, 0);
     GS_TRY(hipGetLastError());
     if (L.ev_pre) GS_TRY(hipEventRecord(L.ev_pre, st));
     auto refresh = [&](bool rows) -> hipError_t {
@@ -1027,7 +1252,7 @@ template <typename T> static hipError_t launch_gs_t(const GsLaunch& L, hipStream
         } else {
             void* args[] = {&g, &t0, &t1};
             GS_TRY(hipLaunchCooperativeKernel(gs_sweep_fn(s), dim3(s.P), dim3(64 * (8 + GS_CW)), args,
-                                              (size_t)16 * s.R * s.k, st));
+                                              gs_sweep_lds(s), st));
         }
         t0 = t1;
     }
@@ -1038,9 +1263,11 @@ template <typename T> static hipError_t launch_gs_t(const GsLaunch& L, hipStream
 
 hipError_t gs_setup(const GsShape& s) {
     if (!s.one && (!gs_sweep_fn(s) || s.P * s.R != s.Up || s.k % s.R != 0)) return hipErrorInvalidValue;
-    if (!s.one && 16 * s.R * s.k > 48 * 1024)
-        GS_TRY(hipFuncSetAttribute(gs_sweep_fn(s), hipFuncAttributeMaxDynamicSharedMemorySize, 16 * s.R * s.k));
-    return hipFuncSetAttribute((const void*)k_gs_inv64, hipFuncAttributeMaxDynamicSharedMemorySize, (int)GS_INV_LDS);
+    auto allow = [](const void* fn, size_t lds) {
+        return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    };
+    if (!s.one && gs_sweep_lds(s) > 48 * 1024) GS_TRY(allow(gs_sweep_fn(s), gs_sweep_lds(s)));
+    return allow((const void*)k_gs_inv64, GS_INV_LDS);
 }
 
 hipError_t launch_gs(const GsLaunch& L, hipStream_t st) {

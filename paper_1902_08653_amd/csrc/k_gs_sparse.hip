@@ -150,7 +150,8 @@ __global__ __launch_bounds__(1024) void k_gsp_matrix(const int32_t* __restrict__
 
 // r = y - H x, one wave per row (r = y where the CSR arrays are malformed: H = 0)
 template <typename T>
-__global__ __launch_bounds__(256) void k_gsp_rows(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
+__global__ __launch_bounds__(256) void k_gsp_rows(const int32_t* __restrict__ rowptr,
+                                                  const int32_t* __restrict__ colidx,
                                                   const cv<T>* __restrict__ val, int B, const cv<T>* __restrict__ y,
                                                   const double2* __restrict__ x, double2* __restrict__ r,
                                                   const uint32_t* __restrict__ status,
@@ -170,7 +171,8 @@ __global__ __launch_bounds__(256) void k_gsp_rows(const int32_t* __restrict__ ro
 
 // b_u = h_u^H r - lambda x_u, one wave per user (zero past U)
 template <typename T>
-__global__ __launch_bounds__(256) void k_gsp_grad(const int32_t* __restrict__ colptr, const int32_t* __restrict__ rowidx,
+__global__ __launch_bounds__(256) void k_gsp_grad(const int32_t* __restrict__ colptr,
+                                                  const int32_t* __restrict__ rowidx,
                                                   const cv<T>* __restrict__ cval, int U, int Up,
                                                   const double2* __restrict__ r, const double2* __restrict__ x,
                                                   double lambda, double2* __restrict__ b,

@@ -127,6 +127,7 @@ struct cdm_plan {
     GsShape gshape;
     void* gs_A = nullptr;
     void* gs_W = nullptr;
+    void* gs_Mt = nullptr;
     void* gs_r = nullptr;
     void* gs_b = nullptr;
     void* gs_x = nullptr;
@@ -244,13 +245,13 @@ static constexpr int kSpKp = 64;   // users per panel of the sparse row-slice en
 
 // One instance on the Gauss-Seidel operator (k_gs.hip) instead of the panel engine or one
 // workgroup.  Its pre-pass forms H^H H, 4 B U^2 multiply-adds that the others do not spend
-// (B U^2 / 1.5e7 us); its sweep then costs 4 us per 512 users, against 4-6 us per 64
+// (B U^2 / 1.5e7 us); its sweep then costs 4 us (per 512 users above 1024), against 4-6 us per 64
 // (look-ahead) or 9-13 us per 128 (two-hop) and 0.5-0.8 us per user in one workgroup.
 // Measured, old / new in us:
 //   complex128 16000 x 2048:  8 sweeps 2396 / 4914, 16 4056 / 5284, 32 7364 / 5576
 //   complex128  7500 x 1500:  4 sweeps 1080 / 1496,  8 1660 / 1540, 32 5190 / 1905
 //   complex64   4096 x 2048:  8 sweeps 1291 / 1658, 16 2254 / 1850
-//   complex128  3000 x 1000:  4 sweeps 1133 /  468, 32 4466 /  715
+//   complex128  3000 x 1000:  4 sweeps 1126 /  508, 40 5373 /  691
 //   complex128   256 x   16:  4 sweeps   56 /   67,  8  103 /   73
 //   complex64    256 x   16:  8 sweeps   73 /   71, 16  134 /   94
 // so the lines are B U <= 1.4e6 (complex128) or 0.8e6 (complex64) per sweep, and 128 or 160
@@ -280,10 +281,11 @@ static int32_t create_gs(cdm_plan* p, cdm_plan** plan) {
     const size_t sq = 16 * (size_t)s.Up * s.Up;
     Arena ar;
     const size_t o_ctr = ar.take(4 * GS_CTR_WORDS + 8 * gs_exchange_words(s));
-    const size_t o_gpart = ar.take((size_t)s.nsplit * s.nblk * 65536);
+    const size_t o_gpart = ar.take(((size_t)s.nwork + s.nblk) * 65536);
     const size_t o_A = ar.take(sq);
     const size_t o_W = ar.take(sq);
     const size_t o_M = ar.take(16 * (size_t)s.npan * s.k * s.k);
+    const size_t o_Mt = ar.take(16 * (size_t)s.npan * s.k * s.k);
     const size_t o_r = ar.take(16 * (size_t)d.B);
     const size_t o_b = ar.take(16 * (size_t)s.Up);
     const size_t o_x = ar.take(16 * (size_t)s.Up);
@@ -302,6 +304,7 @@ static int32_t create_gs(cdm_plan* p, cdm_plan** plan) {
     p->gs_A = b + o_A;
     p->gs_W = b + o_W;
     p->M = b + o_M;
+    p->gs_Mt = b + o_Mt;
     p->gs_r = b + o_r;
     p->gs_b = b + o_b;
     p->gs_x = b + o_x;
@@ -314,7 +317,7 @@ static int32_t create_gs(cdm_plan* p, cdm_plan** plan) {
              "{\"engine\": \"panel\", \"schedule\": \"operator\", \"lookahead_panels\": 0, \"precision\": \"%s\", "
              "\"B\": %d, \"U\": %d, \"panel\": %d, \"rpl\": %d, \"workgroups\": %d, \"npanels\": %d, "
              "\"gram_splits\": %d, \"inner_sweeps\": 0, \"workspace\": %zu}",
-             p->c128 ? "c128" : "c64", d.B, d.U, s.k, s.R, s.one ? 1 : s.P, s.npan, s.nsplit, p->ws_bytes);
+             p->c128 ? "c128" : "c64", d.B, d.U, s.k, s.R, s.one ? 1 : s.P, s.npan, s.nwork, p->ws_bytes);
     p->text = buf;
     st = setup_timing(p);
     if (st) {
@@ -329,6 +332,7 @@ static int32_t solve_gs(cdm_plan* p, const void* H, int64_t ldh, const void* y, 
                         void* x, cdm_info* info, hipStream_t st, const SparseLaunch* sp = nullptr) {
     GsLaunch L;
     L.sp = sp;
+    L.Mt = p->gs_Mt;
     L.kexp = p->gs_kexp;
     L.vs = p->gs_vs;
     L.c128 = p->c128;
@@ -394,6 +398,7 @@ static bool create_sparse_gs(cdm_plan* p) {
     const size_t o_A = ar.take(sq);
     const size_t o_W = ar.take(sq);
     const size_t o_M = ar.take(16 * (size_t)s.npan * s.k * s.k);
+    const size_t o_Mt = ar.take(16 * (size_t)s.npan * s.k * s.k);
     const size_t o_r = ar.take(16 * (size_t)d.B);
     const size_t o_b = ar.take(16 * (size_t)s.Up);
     const size_t o_x = ar.take(16 * (size_t)s.Up);
@@ -414,6 +419,7 @@ static bool create_sparse_gs(cdm_plan* p) {
     p->gs_A = b + o_A;
     p->gs_W = b + o_W;
     p->M = b + o_M;
+    p->gs_Mt = b + o_Mt;
     p->gs_r = b + o_r;
     p->gs_b = b + o_b;
     p->gs_x = b + o_x;
