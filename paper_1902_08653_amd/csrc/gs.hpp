@@ -18,7 +18,7 @@ struct GsShape {
 };
 GsShape gs_shape(int B, int U);
 
-constexpr int GS_CTR_WORDS = 16;   // uint32: [2] abort, [3] status, [4] done
+constexpr int GS_CTR_WORDS = 16;   // uint32: [2] abort, [3] status, [4] done, [6] arrivals
 // 64-bit exchange words after the control words, cleared with them per solve
 size_t gs_exchange_words(const GsShape& s);
 
@@ -34,6 +34,14 @@ struct GsSweepArgs {
     double tol;
     uint64_t timeout_ticks;
     int npan, Up;
+    // what the single-panel sweep forms b anew from (dense channels)
+    const void* H;
+    const void* y;
+    double2* r;
+    uint32_t* arrived;
+    int64_t ld;
+    int B, U;
+    double lambda;
 };
 
 struct GsLaunch {

@@ -28,6 +28,8 @@
 #include "gs.hpp"
 #include "la_common.hpp"
 
+#include <type_traits>
+
 namespace cdm {
 
 namespace {
@@ -994,29 +996,39 @@ __global__ __launch_bounds__(1024) void k_gs_finish(const double2* __restrict__ 
 // gather every delta (tagged words, one memory round trip) into LDS behind one barrier, and
 // each workgroup keeps all of x in theirs: its norms, and with them the decision to stop, are the
 // same bits everywhere and need no exchange.  They are formed while the tile waves work and
-// looked at a sweep later, before x moves on.
+// looked at a sweep later, before x moves on.  With a dense channel's type T the kernel forms b
+// anew itself between the segments of sweeps (r from the workgroups' rows, all wait for all, b from
+// the workgroups' users).
 // Bound by the exchange: 3000 x 1000 complex128, 39 sweeps, 4.0 us each (two panels of 512 with M and W
 // streamed: 8.4), the whole solve 850 -> 700 us.
-template <int R, int KC>
-__global__ __launch_bounds__(64 * (8 + GS_CW), 1) void k_gs_delta(GsSweepArgs a, int t0, int t1) {
-    constexpr int NW = 8, RW = R / NW, k = 64 * KC, GC = KC / GS_CW;
+// after sweep t0 the sweep at which b is formed anew
+__host__ __device__ inline int gs_segment_end(int t0, int t_max) {
+    const int seg = t0 < 2 ? 2 : (t0 < 8 ? 8 : (t0 < 40 ? 40 : (t0 < 200 ? 200 : t_max)));
+    return seg < t_max ? seg : t_max;
+}
+template <typename T> constexpr int gs_rows_per_block() { return 128 / (int)sizeof(cv<T>); }   // one cache line
+template <> constexpr int gs_rows_per_block<void>() { return 1; }
+template <int R, int KC, typename T>
+__global__ __launch_bounds__(64 * (8 + GS_CW), 1) void k_gs_delta(GsSweepArgs a, int t0, int t_end) {
+    constexpr int NW = 8, RW = R / NW, k = 64 * KC, GC = KC / GS_CW, NV = NW + GS_CW, RB = gs_rows_per_block<T>();
     if (*a.done) return;
     __shared__ double2 ds[2][k];
     __shared__ double2 st[2][GS_CW];
+    __shared__ double2 red[NV][RB];
     __shared__ int go[2][GS_CW];
     const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int w = blockIdx.x;
+    const int w = blockIdx.x, P = gridDim.x;
     const bool comm = wid >= NW;
     const int row0 = w * R + (comm ? 0 : wid * RW), i0 = (wid - NW) * 64 * GC + lane;
     double2 V[RW][KC], v[GC], x[GC];
-    auto product = [&](auto row, auto in, double2(&d)[RW]) __attribute__((always_inline)) {
+    auto product = [&](const double2* in, double2(&d)[RW]) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < RW; ++r) d[r] = make_double2(0.0, 0.0);
 #pragma unroll
         for (int q = 0; q < KC; ++q) {
-            const double2 z = in(q);
+            const double2 z = in[lane + 64 * q];
 #pragma unroll
-            for (int r = 0; r < RW; ++r) cfma(d[r], row(r, q), z);
+            for (int r = 0; r < RW; ++r) cfma(d[r], V[r][q], z);
         }
 #pragma unroll
         for (int r = 0; r < RW; ++r) {
@@ -1024,16 +1036,58 @@ __global__ __launch_bounds__(64 * (8 + GS_CW), 1) void k_gs_delta(GsSweepArgs a,
             d[r].y = group_sum<1>(d[r].y);
         }
     };
-    auto publish = [&](const double2(&d)[RW], int t) __attribute__((always_inline)) {
+    // these rows of M times b; a few columns at a time, as V lives next to them
+    auto m_product = [&](const double2* b, double2(&d)[RW]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            const double2* const m = a.M + (int64_t)(row0 + r) * k;
+            d[r] = make_double2(0.0, 0.0);
+#pragma unroll 4
+            for (int q = 0; q < KC; ++q) cfma(d[r], m[lane + 64 * q], b[lane + 64 * q]);
+            d[r].x = group_sum<1>(d[r].x);
+            d[r].y = group_sum<1>(d[r].y);
+        }
+    };
+    auto publish = [&](const double2(&d)[RW], int slot, int t) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < RW; ++r)
-            if (lane == r) gs_put(a.xch + (int64_t)(t & 1) * k * 3, k, row0 + r, d[r], (uint32_t)t);
+            if (lane == r) gs_put(a.xch + (int64_t)slot * k * 3, k, row0 + r, d[r], (uint32_t)t);
+    };
+    // bounded waits: given up after the time limit, or with the others
+    uint64_t tw = 0;
+    auto expired = [&]() __attribute__((always_inline)) -> bool {
+        const uint64_t now = wall_clock64();
+        if (!tw) tw = now;
+        if (!ld_relaxed(a.abort_flag) && now - tw <= a.timeout_ticks) return false;
+        if (lane == 0) st_relaxed(a.abort_flag, 1u);
+        return true;
+    };
+    // the k values of a slot into v and `out`: 1, or 3 when given up (per communicating wave)
+    auto gather = [&](int slot, int t, double2* out) __attribute__((always_inline)) -> int {
+        bool ok = false;
+        int g = 1;
+        tw = 0;
+        for (;;) {
+            if (!ok) {
+                ok = true;
+#pragma unroll
+                for (int q = 0; q < GC; ++q)
+                    ok &= gs_get(a.xch + (int64_t)slot * k * 3, k, i0 + 64 * q, (uint32_t)t, v[q]);
+            }
+            if (__all(ok)) break;
+            if (expired()) {
+                g = 3;
+                break;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < GC; ++q) out[i0 + 64 * q] = v[q];
+        return g;
     };
     if (!comm) {
         double2 d[RW];   // the first delta is M b
-        product([&](int r, int q) { return a.M[(int64_t)(row0 + r) * k + lane + 64 * q]; },
-                [&](int q) { return a.b[lane + 64 * q]; }, d);
-        publish(d, t0 + 1);
+        m_product(a.b, d);
+        publish(d, (t0 + 1) & 1, t0 + 1);
 #pragma unroll
         for (int r = 0; r < RW; ++r) {
             const double2* const p = a.W + (int64_t)(row0 + r) * k;   // scalar base, one offset register
@@ -1057,30 +1111,99 @@ __global__ __launch_bounds__(64 * (8 + GS_CW), 1) void k_gs_delta(GsSweepArgs a,
         }
         return a.tol > 0.0 && !(S > 2.0 * a.tol * a.tol * X) && sqrt(S) <= a.tol * sqrt(X);
     };
-    int code = 1, t = t0 + 1, par = 0;   // code: 1 goes on, 2 met, 3 given up
+    // b anew from H, y and x, and the first delta of sweep t + 1 from it; false: given up.  Rows
+    // and users are dealt to the workgroups; r passes through memory, b through a slot.
+    int round = 0;
+    auto anew = [&](int t, int par) -> bool {
+        if constexpr (!std::is_void_v<T>) {
+            double2* const xs = ds[par ^ 1];
+            const cv<T>* const H = (const cv<T>*)a.H;
+            if (comm) {
+#pragma unroll
+                for (int q = 0; q < GC; ++q) xs[i0 + 64 * q] = x[q];
+            }
+            __syncthreads();
+            for (int blk = w; blk * RB < a.B; blk += P) {   // r: a lane's row and column group
+                const int row = blk * RB + lane % RB, rc = min(row, a.B - 1);
+                constexpr int G = 64 / RB;
+                double2 s = make_double2(0.0, 0.0);
+#pragma unroll 4
+                for (int u = wid * G + lane / RB; u < a.U; u += NV * G) cfma(s, to_d(H[(int64_t)u * a.ld + rc]), xs[u]);
+#pragma unroll
+                for (int m = RB; m < 64; m *= 2) {
+                    s.x += __shfl_xor(s.x, m);
+                    s.y += __shfl_xor(s.y, m);
+                }
+                if (lane < RB) red[wid][lane] = s;
+                __syncthreads();
+                if (wid == 0 && lane < RB && row < a.B) {
+                    double2 z = to_d(((const cv<T>*)a.y)[row]);
+#pragma unroll
+                    for (int p = 0; p < NV; ++p) {
+                        z.x -= red[p][lane].x;
+                        z.y -= red[p][lane].y;
+                    }
+                    a.r[row] = z;
+                }
+                __syncthreads();
+            }
+            ++round;
+            if (wid == 0) {   // this wave wrote the rows of r: out to memory, then all wait for all
+                __threadfence();
+                if (lane == 0) atomicAdd(a.arrived, 1u);
+                int g = 1;
+                tw = 0;
+                while (ld_relaxed(a.arrived) < (uint32_t)(round * P))
+                    if (expired()) {
+                        g = 3;
+                        break;
+                    }
+                __threadfence();
+                if (lane == 0) go[0][0] = g;
+            }
+            __syncthreads();
+            if (go[0][0] == 3) return false;
+            if (!comm) {
+                double2 d[RW];
+#pragma unroll
+                for (int r = 0; r < RW; ++r) {
+                    const int u = row0 + r;
+                    const cv<T>* const h = H + (int64_t)min(u, a.U - 1) * a.ld;
+                    double2 s = make_double2(0.0, 0.0);
+#pragma unroll 4
+                    for (int i = lane; i < a.B; i += 64) cfma_conj(s, to_d(h[i]), a.r[i]);
+                    s.x = group_sum<1>(s.x);
+                    s.y = group_sum<1>(s.y);
+                    d[r] = u < a.U ? make_double2(s.x - a.lambda * xs[u].x, s.y - a.lambda * xs[u].y)
+                                   : make_double2(0.0, 0.0);
+                }
+                publish(d, 2, t + 1);
+            }
+            __syncthreads();   // go is free
+            if (comm) {
+                const int g = gather(2, t + 1, ds[par]);
+                if (lane == 0) go[0][wid - NW] = g;
+            }
+            __syncthreads();
+            int c = 1;
+#pragma unroll
+            for (int q = 0; q < GS_CW; ++q) c = max(c, go[0][q]);
+            if (c == 3) return false;
+            if (!comm) {
+                double2 d[RW];
+                m_product(ds[par], d);
+                publish(d, (t + 1) & 1, t + 1);
+            }
+            __syncthreads();   // go and ds are free
+        }
+        return true;
+    };
+    bool stop = false;
+    int code = 1, t = t0 + 1, par = 0, ts = t0;   // code: 1 goes on, 2 met, 3 given up
+    int t1 = gs_segment_end(t0, t_end);
     for (;; ++t, par ^= 1) {
         if (comm) {
-            int g = 1;
-            uint64_t tw = 0;
-            bool ok = false;
-            for (;;) {
-                if (!ok) {
-                    ok = true;
-#pragma unroll
-                    for (int q = 0; q < GC; ++q)
-                        ok &= gs_get(a.xch + (int64_t)(t & 1) * k * 3, k, i0 + 64 * q, (uint32_t)t, v[q]);
-                }
-                if (__all(ok)) break;
-                const uint64_t now = wall_clock64();   // bounded: given up after the time limit, or with the others
-                if (!tw) tw = now;
-                if (ld_relaxed(a.abort_flag) || now - tw > a.timeout_ticks) {
-                    if (lane == 0) st_relaxed(a.abort_flag, 1u);
-                    g = 3;
-                    break;
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < GC; ++q) ds[par][i0 + 64 * q] = v[q];
+            const int g = gather(t & 1, t, ds[par]);
             if (lane == 0) go[par][wid - NW] = g;
         }
         __syncthreads();
@@ -1089,10 +1212,10 @@ __global__ __launch_bounds__(64 * (8 + GS_CW), 1) void k_gs_delta(GsSweepArgs a,
         if (code == 3) break;
         if (!comm && t < t1) {
             double2 d[RW];
-            product([&](int r, int q) { return V[r][q]; }, [&](int q) { return ds[par][lane + 64 * q]; }, d);
-            publish(d, t + 1);
+            product(ds[par], d);
+            publish(d, (t + 1) & 1, t + 1);
         }
-        if (a.tol > 0.0 && t - 1 > t0 && met(par ^ 1)) {
+        if (a.tol > 0.0 && t - 1 > ts && met(par ^ 1)) {
             code = 2;
             break;
         }
@@ -1109,19 +1232,23 @@ __global__ __launch_bounds__(64 * (8 + GS_CW), 1) void k_gs_delta(GsSweepArgs a,
             s2 = group_sum<1>(s2);
             if (lane == 0) st[par][wid - NW] = make_double2(s1, s2);
         }
-        if (t == t1) break;
-    }
-    bool stop = code != 1;
-    if (code == 1) {
+        if (t < t1) continue;
         __syncthreads();
         stop = met(par);
+        if (stop || t == t_end) break;
+        if (!anew(t, par)) {
+            code = 3;
+            break;
+        }
+        ts = t;
+        t1 = gs_segment_end(t, t_end);
     }
     if (w != 0 || !comm) return;
 #pragma unroll
     for (int q = 0; q < GC; ++q) a.x[i0 + 64 * q] = x[q];
     if (wid == NW && lane == 0) {
         gs_info(a.info, code == 1 ? t : t - 1, S, X, a.tol, code != 3);
-        if (stop) *a.done = 1;
+        if (stop || code != 1) *a.done = 1;
     }
 }
 
@@ -1159,16 +1286,21 @@ GsShape gs_shape(int B, int U) {
 }
 
 size_t gs_exchange_words(const GsShape& s) {
-    return 3 * ((size_t)s.npan * 2 * s.k + 4 * (size_t)s.P);
+    return s.npan == 1 ? 9 * (size_t)s.k : 3 * ((size_t)s.npan * 2 * s.k + 4 * (size_t)s.P);
 }
 
-// the sweep kernel of a tiling: its R and k are the kernel's own (NULL: none is built)
-static const void* gs_sweep_fn(const GsShape& s) {
+// all sweeps of a dense channel in one launch
+static bool gs_whole(const GsShape& s, int B, int U) {
+    return !s.one && s.k <= 512 && s.npan == 1 && (int64_t)B * U <= (int64_t)12000 * s.P;
+}
+// the sweep kernel of a tiling: its R and k are the kernel's own (NULL: none is built).  SRC: float
+// or double, or void where b is formed anew by launches in between
+template <typename SRC> static const void* gs_sweep_fn(const GsShape& s) {
     if (s.npan == 1) {
         if (s.R != GS_DELTA_R) return nullptr;
-        if (s.k == 256) return (const void*)k_gs_delta<GS_DELTA_R, 4>;
-        if (s.k == 512) return (const void*)k_gs_delta<GS_DELTA_R, 8>;
-        if (s.k == 1024) return (const void*)k_gs_delta<GS_DELTA_R, 16>;
+        if (s.k == 256) return (const void*)k_gs_delta<GS_DELTA_R, 4, SRC>;
+        if (s.k == 512) return (const void*)k_gs_delta<GS_DELTA_R, 8, SRC>;
+        if (s.k == 1024 && std::is_void_v<SRC>) return (const void*)k_gs_delta<GS_DELTA_R, 16, void>;
         return nullptr;
     }
     if (s.k == 512 && s.R == 16) return (const void*)k_gs_sweep<16, 8, 8>;
@@ -1242,19 +1374,31 @@ template <typename T> static hipError_t launch_gs_t(const GsLaunch& L, hipStream
     g.timeout_ticks = L.timeout_ticks;
     g.npan = s.npan;
     g.Up = s.Up;
-    int t0 = 0;
-    for (int seg = 2; t0 < L.T_max; seg = seg == 2 ? 8 : seg * 5) {
+    g.H = L.H;
+    g.y = L.y;
+    g.r = r;
+    g.arrived = L.ctr + 6;
+    g.ld = L.ld;
+    g.B = L.B;
+    g.U = L.U;
+    g.lambda = L.lambda;
+    // A cooperative launch costs 22 us of idle time around it.  Up to 512 users of a dense channel
+    // one launch runs all sweeps and forms b anew itself; 40 sweeps, launches / in one: 400 x 150
+    // 235 / 199 us, 800 x 300 300 / 271, 1500 x 500 335 / 320.  At 1024 users V leaves no registers
+    // for the loads of the two products with H (3000 x 1000: 44 us each time against 32), and tall
+    // channels want more workgroups for them than the sweep has.
+    const bool whole = gs_whole(s, L.B, L.U) && !L.sp;
+    const void* const fn = s.one ? nullptr : (whole ? gs_sweep_fn<T>(s) : gs_sweep_fn<void>(s));
+    for (int t0 = 0, t1; t0 < L.T_max; t0 = t1) {
         GS_TRY(refresh(t0 > 0 || L.x0));
-        int t1 = (seg >= 1000 || L.T_max < seg) ? L.T_max : seg;   // 2, 8, 40, 200, then to the end
+        t1 = whole ? L.T_max : gs_segment_end(t0, L.T_max);
         if (s.one) {
             hipLaunchKernelGGL(k_gs_one, dim3(1), dim3(1024), 0, st, W, M, b, x, L.U, t0, t1, L.tol, done, L.info);
             GS_TRY(hipGetLastError());
         } else {
             void* args[] = {&g, &t0, &t1};
-            GS_TRY(hipLaunchCooperativeKernel(gs_sweep_fn(s), dim3(s.P), dim3(64 * (8 + GS_CW)), args,
-                                              gs_sweep_lds(s), st));
+            GS_TRY(hipLaunchCooperativeKernel(fn, dim3(s.P), dim3(64 * (8 + GS_CW)), args, gs_sweep_lds(s), st));
         }
-        t0 = t1;
     }
     if (L.ev_sweep) GS_TRY(hipEventRecord(L.ev_sweep, st));
     hipLaunchKernelGGL(k_gs_finish<T>, dim3(1), dim3(1024), 0, st, x, L.U, (cv<T>*)L.x, L.ctr + 3, L.info);
@@ -1262,11 +1406,11 @@ template <typename T> static hipError_t launch_gs_t(const GsLaunch& L, hipStream
 }
 
 hipError_t gs_setup(const GsShape& s) {
-    if (!s.one && (!gs_sweep_fn(s) || s.P * s.R != s.Up || s.k % s.R != 0)) return hipErrorInvalidValue;
+    if (!s.one && (!gs_sweep_fn<void>(s) || s.P * s.R != s.Up || s.k % s.R != 0)) return hipErrorInvalidValue;
     auto allow = [](const void* fn, size_t lds) {
         return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     };
-    if (!s.one && gs_sweep_lds(s) > 48 * 1024) GS_TRY(allow(gs_sweep_fn(s), gs_sweep_lds(s)));
+    if (!s.one && gs_sweep_lds(s) > 0) GS_TRY(allow(gs_sweep_fn<void>(s), gs_sweep_lds(s)));
     return allow((const void*)k_gs_inv64, GS_INV_LDS);
 }
 
