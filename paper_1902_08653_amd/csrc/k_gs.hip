@@ -622,92 +622,138 @@ __device__ __forceinline__ void gs_info(cdm_info* info, int sweeps, double S, do
 
 // Sweeps t0 + 1 .. t1 of a single panel of at most 128 users, in one workgroup: with one
 // panel the deltas follow each other by delta <- V delta, V = -M L^H, so V stays in
-// registers (128 x 128 complex FP64 = 64 VGPRs of 1024 threads) and a sweep is one product
-// and two barriers.  Thread: row group of 2 rows x 8 columns (16 lanes to a row pair).
-__global__ __launch_bounds__(1024) void k_gs_one(const double2* __restrict__ V, const double2* __restrict__ M,
-                                                 const double2* __restrict__ b, double2* __restrict__ x, int U,
-                                                 int t0, int t1, double tol, uint32_t* __restrict__ done,
-                                                 cdm_info* __restrict__ info) {
+// registers (128 x 128 complex FP64 = 128 VGPRs of 512 threads) and a sweep is one product and
+// one barrier.  Thread: 4 rows x 8 columns, 16 lanes to a row.  The eight sums of 4 rows over
+// the 16 lanes are formed by halving: a lane keeps half of its sums in each of three exchanges
+// (with lane 15 - i, then 7 - i, then i ^ 2) and ends with one part of one delta, and of x.
+// The norms of a sweep are formed while the next product's operands come from LDS, and
+// looked at by the last wave during the product after that, so a stop is known two sweeps
+// later and x of the last three is kept.
+// Bound: the product's 1024 cycles of FP64 FMA per SIMD, its 512 cycles of LDS reads, and the
+// chain of sums and barrier.  256 x 128, 60 sweeps, the whole solve: 156 us (1.5 us a sweep); 1024
+// threads with two rows each, every sum in every lane and the stop looked at by all of them
+// between the sweeps 182 us (1.8).
+template <int CTRL> __device__ __forceinline__ void halve(double& a, double b, bool upper) {
+    // lanes with `upper` keep b, the others a: + what the partner lane has of the same
+    const double mine = upper ? b : a, give = upper ? a : b;
+    a = mine + dpp_take<CTRL, 0xf>(give);
+}
+__global__ __launch_bounds__(512) void k_gs_one(const double2* __restrict__ V, const double2* __restrict__ M,
+                                                const double2* __restrict__ b, double2* __restrict__ x, int U,
+                                                int t0, int t1, double tol, uint32_t* __restrict__ done,
+                                                cdm_info* __restrict__ info) {
     if (*done) return;
     __shared__ double2 ds[2][128];
-    __shared__ double2 st[2][16];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int cl = lane & 15, r0 = wv * 8 + (lane >> 4) * 2;
-    double2 w[2][8], xv[2], d[2];
+    __shared__ double st[2][16];
+    __shared__ int flag[2];
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cl = lane & 15, r0 = wv * 16 + (lane >> 4) * 4;
+    const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2, b0 = lane & 1;
+    const int part = 2 * (r0 + 2 * (int)b3 + (int)b2) + (int)b1;   // this lane's double of x and delta
+    double2 w[4][8], d[4];
     // delta of sweep t0 + 1 is M b
     if (tid < 128) ds[1][tid] = b[tid];
+    if (tid < 2) flag[tid] = 0;
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
+    for (int p = 0; p < 4; ++p)
 #pragma unroll
         for (int q = 0; q < 8; ++q) w[p][q] = M[(r0 + p) * 128 + cl + 16 * q];
-#pragma unroll
-    for (int p = 0; p < 2; ++p) xv[p] = x[r0 + p];
+    double xv = ((const double*)x)[part], xp = xv, xpp = xv;   // x after this sweep and the two before
     __syncthreads();
-    auto product = [&](const double2* in) __attribute__((always_inline)) {
-        d[0] = d[1] = make_double2(0.0, 0.0);
+    double2 v[8];
+    auto fetch = [&](const double2* in) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const double2 v = in[cl + 16 * q];
-            cfma(d[0], w[0][q], v);
-            cfma(d[1], w[1][q], v);
-        }
+        for (int q = 0; q < 8; ++q) v[q] = in[cl + 16 * q];
     };
-    product(ds[1]);
+    auto product = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
+        for (int p = 0; p < 4; ++p) d[p] = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int p = 0; p < 4; ++p) cfma(d[p], w[p][q], v[q]);
+    };
+    fetch(ds[1]);
+    product();
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
 #pragma unroll
         for (int q = 0; q < 8; ++q) w[p][q] = V[(r0 + p) * 128 + cl + 16 * q];
-    int t = t0;
     double S = 0.0, X = 0.0;
-    bool stop = false;
-    while (t < t1 && !stop) {
-        double2* out = ds[(t - t0) & 1];
-        if (t > t0) product(ds[(t - t0 + 1) & 1]);
-        double s1 = 0.0, s2 = 0.0;
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            d[p].x += row_ror<1>(d[p].x);
-            d[p].y += row_ror<1>(d[p].y);
-            d[p].x += row_ror<2>(d[p].x);
-            d[p].y += row_ror<2>(d[p].y);
-            d[p].x += row_ror<4>(d[p].x);
-            d[p].y += row_ror<4>(d[p].y);
-            d[p].x += row_ror<8>(d[p].x);
-            d[p].y += row_ror<8>(d[p].y);
-            xv[p].x += d[p].x;
-            xv[p].y += d[p].y;
-            if (cl == 0) out[r0 + p] = d[p];
-            s1 += cabs2d(d[p]);
-            s2 += cabs2d(xv[p]);
-        }
-        s1 = swap_add<32>(swap_add<16>(s1));   // over the wave's four row pairs
-        s2 = swap_add<32>(swap_add<16>(s2));
-        if (lane == 0) st[t & 1][wv] = make_double2(s1, s2);
+    auto norms = [&](int t, double dv) __attribute__((always_inline)) {   // even lanes |delta|^2, odd lanes |x|^2
+        double s = b0 ? xv * xv : dv * dv;
+        s += row_ror<8>(s);
+        s += row_ror<4>(s);
+        s += dpp_take<0x4e, 0xf>(s);
+        s = swap_add<32>(swap_add<16>(s));
+        if (lane < 2) st[t & 1][2 * wv + lane] = s;
+    };
+    auto decide = [&](int t) __attribute__((always_inline)) -> bool {   // by the last wave, of sweep t
+        double s = st[t & 1][cl];
+        s += row_ror<8>(s);
+        s += row_ror<4>(s);
+        s += row_ror<2>(s);
+        S = lane_value(s, 0);
+        X = lane_value(s, 1);
+        // the two roots only where they can decide: FP64 roots cost as much as the product
+        return tol > 0.0 && !(S > 2.0 * tol * tol * X) && sqrt(S) <= tol * sqrt(X);
+    };
+    int t = t0 + 1, back = 0;   // the sweep that ends it is t - back
+    double dv;
+    for (;; ++t) {
+        // rows (0, 1) | (2, 3), then one row, then its real | imaginary part, then both lanes
+        halve<0x140>(d[0].x, d[2].x, b3);
+        halve<0x140>(d[0].y, d[2].y, b3);
+        halve<0x140>(d[1].x, d[3].x, b3);
+        halve<0x140>(d[1].y, d[3].y, b3);
+        halve<0x141>(d[0].x, d[1].x, b2);
+        halve<0x141>(d[0].y, d[1].y, b2);
+        halve<0x4e>(d[0].x, d[0].y, b1);
+        dv = d[0].x + dpp_take<0xb1, 0xf>(d[0].x);
+        xpp = xp;
+        xp = xv;
+        xv += dv;
+        if (!b0) ((double*)ds[t & 1])[part] = dv;
         __syncthreads();
-        ++t;
-        if (tol > 0.0 || t == t1) {   // the 16 waves' parts: a lane each, summed over the row of 16
-            const double2 v = st[(t - 1) & 1][cl];
-            S = v.x;
-            X = v.y;
-            S += row_ror<1>(S);
-            X += row_ror<1>(X);
-            S += row_ror<2>(S);
-            X += row_ror<2>(X);
-            S += row_ror<4>(S);
-            X += row_ror<4>(X);
-            S += row_ror<8>(S);
-            X += row_ror<8>(X);
-            // the two roots only where they can decide: FP64 roots cost as much as the product
-            stop = tol > 0.0 && !(S > 2.0 * tol * tol * X) && sqrt(S) <= tol * sqrt(X);
+        if (t == t1) break;
+        fetch(ds[t & 1]);
+        if (tol > 0.0) {   // while the deltas come from LDS
+            if (flag[t & 1]) {
+                back = 2;
+                break;
+            }
+            norms(t, dv);
+            if (wv == 7 && t - 1 > t0) {
+                const bool met = decide(t - 1);
+                if (lane == 0) flag[(t - 1) & 1] = met;
+            }
         }
+        product();
     }
-#pragma unroll
-    for (int p = 0; p < 2; ++p)
-        if (cl == 0) x[r0 + p] = xv[p];
-    if (tid == 0) {
-        gs_info(info, t, S, X, tol, true);
-        if (stop) *done = 1;
+    if (back == 0) {   // t == t1: the decisions of the last three sweeps
+        norms(t, dv);
+        __syncthreads();
+        if (wv == 7) {
+            int which = -1;
+            if (tol > 0.0 && flag[t & 1])
+                which = 2;   // S, X are still that sweep's
+            else if (t - 1 > t0 && decide(t - 1))
+                which = 1;
+            else if (decide(t))
+                which = 0;
+            if (lane == 0) {
+                gs_info(info, t - max(which, 0), S, X, tol, true);
+                if (which >= 0) *done = 1;
+                flag[(t + 1) & 1] = max(which, 0);
+            }
+        }
+        __syncthreads();
+        back = flag[(t + 1) & 1];
+    } else if (wv == 7 && lane == 0) {
+        gs_info(info, t - 2, S, X, tol, true);
+        *done = 1;
     }
+    if (!b0) ((double*)x)[part] = back == 2 ? xpp : (back == 1 ? xp : xv);
 }
 
 // Sweeps t0 + 1 .. t1 over several workgroups (cooperative launch).  Workgroup w owns R
@@ -1393,7 +1439,7 @@ template <typename T> static hipError_t launch_gs_t(const GsLaunch& L, hipStream
         GS_TRY(refresh(t0 > 0 || L.x0));
         t1 = whole ? L.T_max : gs_segment_end(t0, L.T_max);
         if (s.one) {
-            hipLaunchKernelGGL(k_gs_one, dim3(1), dim3(1024), 0, st, W, M, b, x, L.U, t0, t1, L.tol, done, L.info);
+            hipLaunchKernelGGL(k_gs_one, dim3(1), dim3(512), 0, st, W, M, b, x, L.U, t0, t1, L.tol, done, L.info);
             GS_TRY(hipGetLastError());
         } else {
             void* args[] = {&g, &t0, &t1};
