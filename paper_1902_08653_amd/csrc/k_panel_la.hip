@@ -131,10 +131,16 @@ __global__ __launch_bounds__((la_threads<T, KP>()), 1) void k_cd_panel_la(PanelA
             if (!go) break;
             const char* src = reinterpret_cast<const char*>(a.X + (int64_t)(j % np) * KP * KP) + lane * 16;
             char* dst = reinterpret_cast<char*>(Xs);
-#pragma unroll 4
-            for (int off = 0; off < KP * KP * (int)sizeof(V); off += 1024)
-                __builtin_amdgcn_global_load_lds(src + off, (__attribute__((address_space(3))) void*)(dst + off), 16, 0,
-                                                 0);
+            // complex128 (64 KB): at most ten loads in flight, so that the control wave's words do
+            // not wait behind all of them (46.7 -> 45.0 ms; with seven the stage falls behind, 51.0)
+#pragma unroll 1
+            for (int o4 = 0; o4 < KP * KP * (int)sizeof(V); o4 += 4096) {
+#pragma unroll
+                for (int off = o4; off < o4 + 4096; off += 1024)
+                    __builtin_amdgcn_global_load_lds(src + off, (__attribute__((address_space(3))) void*)(dst + off), 16,
+                                                     0, 0);
+                if (sizeof(T) == 8) __builtin_amdgcn_s_waitcnt(0x0F76);   // vmcnt <= 6, the others at their maxima
+            }
             wave_drain_vmem();
             if (lane == 0) lds_set(&xs_ready, j + 1);
         }
@@ -160,15 +166,30 @@ __global__ __launch_bounds__((la_threads<T, KP>()), 1) void k_cd_panel_la(PanelA
         // are zero, so their delta is zero), and rows past B keep r = 0.
         // panel column of this wave's c-th column
         auto pcol = [&](int c) { return OWN_DELTA ? wu * NC + c : wu + LA_NWT * c; };
-        auto load_tile = [&](Raw(&dst)[NC][RPL], int K) {
+        // eighths e0 .. e1 - 1 of the wave's columns of panel K
+        auto load_part = [&](Raw(&dst)[NC][RPL], int K, int e0, int e1) __attribute__((always_inline)) {
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
+                if (c * 8 < e0 * NC || c * 8 >= e1 * NC) continue;
                 const int col = min(K * KP + pcol(c), U - 1);
 #pragma unroll
                 for (int q = 0; q < RPL; ++q) {
                     const uint32_t row = (uint32_t)min(row0 + lane + 64 * q, B - 1);
                     dst[c][q] = a.src.load_raw(col, row, a.ld);
                 }
+            }
+        };
+        auto load_tile = [&](Raw(&dst)[NC][RPL], int K) __attribute__((always_inline)) { load_part(dst, K, 0, 8); };
+        // A workgroup's memory operations complete in about the order of their issue, so the
+        // control wave's words wait behind a panel's 64 KB where they are asked for at once.
+        // complex128: in four pieces over the step, kept apart by scheduling barriers
+        // (16384 x 8192: 51.1 -> 46.7 ms; halves 49.1, all after the partials 53.7).
+        constexpr bool PACED = !OWN_DELTA;
+        auto load_piece = [&](Raw(&dst)[NC][RPL], int K, int e0, int e1) __attribute__((always_inline)) {
+            if constexpr (PACED) {
+                __builtin_amdgcn_sched_barrier(0);
+                load_part(dst, K, e0, e1);
+                __builtin_amdgcn_sched_barrier(0);
             }
         };
         auto tile_col = [&](int K, int c) { return min(K * KP + pcol(c), U - 1); };
@@ -250,6 +271,7 @@ __global__ __launch_bounds__((la_threads<T, KP>()), 1) void k_cd_panel_la(PanelA
 #define CDM_LA_TSTEP(cur, nn)                                                                         \
     {                                                                                                 \
         if (!wait_b(q)) goto tdone;                                                                   \
+        load_piece(nn, (K + 2) % np, 5, 7); /* the rest of panel K+2, which the last step began */   \
         if constexpr (OWN_DELTA) {                                                                    \
             /* delta of this wave's columns j = wu NC + c; column v of the packed M holds rows        \
                v..KP-1 at offset v KP - v(v-1)/2.  LOCALB: b = q_K - X_K delta_{K-1}, so              \
@@ -324,6 +346,7 @@ __global__ __launch_bounds__((la_threads<T, KP>()), 1) void k_cd_panel_la(PanelA
             tbar();                                                                                   \
             if (bad) goto tdone;                                                                      \
             if (tid == 0) lds_add(&x_cnt, LA_NWT); /* every wave is done reading Xs */                \
+            load_piece(nn, (K + 2) % np, 7, 8);                                                       \
             if (tid < KP) {                                                                           \
                 V s_ = dpart[0][tid];                                                                 \
                 for (int k = 1; k < NS; ++k) {                                                        \
@@ -355,8 +378,10 @@ __global__ __launch_bounds__((la_threads<T, KP>()), 1) void k_cd_panel_la(PanelA
                 r[qq].y -= s_.y;                                                                      \
             }                                                                                         \
         }                                                                                             \
-        load_tile(cur, (K + 3) % np); /* cur is free: stream panel K+3 into it */                    \
+        if constexpr (!PACED) load_tile(cur, (K + 3) % np); /* cur is free: stream panel K+3 into it */ \
+        load_piece(cur, (K + 3) % np, 0, 4);                                                          \
         partial(nn, (K + 2) % np, q + 2); /* look-ahead partials of panel K+2 from r after K */      \
+        load_piece(cur, (K + 3) % np, 4, 5);                                                          \
         K = (K + 1 < np) ? K + 1 : 0;                                                                 \
         ++q;                                                                                          \
     }
@@ -392,8 +417,10 @@ __global__ __launch_bounds__((la_threads<T, KP>()), 1) void k_cd_panel_la(PanelA
         }
         return true;
     };
-    // exchange buffers of tagged words: part [2][KP][P][NW] (slot, column, workgroup),
-    // gbuf [2][KP][2][NW] (slot, column, {b, x})
+    // exchange buffers of tagged words: part [2][KP][NW][P] (slot, column, word, workgroup),
+    // gbuf [2][2][NW][KP] (slot, {b, x}, word, column): a wave's loads of a word are contiguous
+    // (16384 x 8192 complex128:
+    // 53.4 -> 51.1 ms)
     using TG = Tagged<T>;
     constexpr int NW = TG::NW;
     uint64_t* part64 = reinterpret_cast<uint64_t*>(a.part);
@@ -422,13 +449,13 @@ __global__ __launch_bounds__((la_threads<T, KP>()), 1) void k_cd_panel_la(PanelA
 #pragma unroll
         for (int i = 0; i < KL; ++i) {
             const int j = lane + 64 * i;
-            if (j < KP) TG::put(part64 + (((int64_t)(s & 1) * KP + j) * P + w) * NW, psh[s & 1][j], (uint32_t)s + 1);
+            if (j < KP) TG::put(part64 + ((int64_t)(s & 1) * KP + j) * NW * P + w, psh[s & 1][j], (uint32_t)s + 1, P);
         }
     };
     // reducer: wait for the P partials of column j = w of sequence s and sum them (fixed
     // order per lane, then a fixed butterfly); uniform result
     auto gather_partials = [&](int s, V& out) -> bool {
-        const uint64_t* src = part64 + ((int64_t)(s & 1) * KP + w) * P * NW;
+        const uint64_t* src = part64 + ((int64_t)(s & 1) * KP + w) * NW * P;
         const uint32_t tag = (uint32_t)s + 1;
         V v[4];
         bool have[4];
@@ -442,7 +469,7 @@ __global__ __launch_bounds__((la_threads<T, KP>()), 1) void k_cd_panel_la(PanelA
             V nv[4];
             bool ok4[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) ok4[k] = TG::get(src + (int64_t)min(lane + 64 * k, P - 1) * NW, tag, nv[k]);
+            for (int k = 0; k < 4; ++k) ok4[k] = TG::get(src + min(lane + 64 * k, P - 1), tag, nv[k], P);
             bool miss = false;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -480,9 +507,9 @@ __global__ __launch_bounds__((la_threads<T, KP>()), 1) void k_cd_panel_la(PanelA
         bool miss = false;
 #pragma unroll
         for (int i = 0; i < KL; ++i) {
-            const uint64_t* q0 = gb64 + (((int64_t)(q & 1) * KP + min(lane + 64 * i, KP - 1)) * 2) * NW;
+            const uint64_t* q0 = gb64 + (q & 1) * 2 * NW * KP + min(lane + 64 * i, KP - 1);
             V nb, nx;
-            const bool okb = TG::get(q0, tag, nb), okx = TG::get(q0 + NW, tag, nx);
+            const bool okb = TG::get(q0, tag, nb, KP), okx = TG::get(q0 + NW * KP, tag, nx, KP);
             if (!ghb[i] && okb) {
                 gbv[i] = nb;
                 ghb[i] = true;
@@ -527,9 +554,9 @@ __global__ __launch_bounds__((la_threads<T, KP>()), 1) void k_cd_panel_la(PanelA
             V b;
             b.x = g.x - lambda * xo.x;
             b.y = g.y - lambda * xo.y;
-            uint64_t* q0 = gb64 + (((int64_t)(s & 1) * KP + w) * 2) * NW;
-            TG::put(q0, b, (uint32_t)s + 1);
-            TG::put(q0 + NW, xo, (uint32_t)s + 1);
+            uint64_t* q0 = gb64 + (s & 1) * 2 * NW * KP + w;
+            TG::put(q0, b, (uint32_t)s + 1, KP);
+            TG::put(q0 + NW * KP, xo, (uint32_t)s + 1, KP);
         }
     };
     // the same, loading x_j and bias_j of panel K itself (where they cannot be loaded
@@ -546,9 +573,9 @@ __global__ __launch_bounds__((la_threads<T, KP>()), 1) void k_cd_panel_la(PanelA
             V b;
             b.x = g.x - lambda * xo.x;
             b.y = g.y - lambda * xo.y;
-            uint64_t* q0 = gb64 + (((int64_t)(s & 1) * KP + w) * 2) * NW;
-            TG::put(q0, b, (uint32_t)s + 1);
-            TG::put(q0 + NW, xo, (uint32_t)s + 1);
+            uint64_t* q0 = gb64 + (s & 1) * 2 * NW * KP + w;
+            TG::put(q0, b, (uint32_t)s + 1, KP);
+            TG::put(q0 + NW * KP, xo, (uint32_t)s + 1, KP);
         }
     };
     auto stage_M = [&](int K, int buf) {

@@ -37,15 +37,17 @@ template <> struct Tagged<double> {
                            (unsigned long long)((payload & 0xffffffffffffull) | ((uint64_t)(tag & 0xffffu) << 48)),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __device__ static void put(uint64_t* p, double2 v, uint32_t tag) {
+    // the words of a value lie n apart (n = 1: a record; more: planes of n words, in which a
+    // wave's loads of one word are contiguous)
+    __device__ static void put(uint64_t* p, double2 v, uint32_t tag, int n = 1) {
         const uint64_t a = (uint64_t)__double_as_longlong(v.x), b = (uint64_t)__double_as_longlong(v.y);
         st48(p + 0, a, tag);
-        st48(p + 1, (a >> 48) | (b << 16), tag);
-        st48(p + 2, b >> 32, tag);
+        st48(p + n, (a >> 48) | (b << 16), tag);
+        st48(p + 2 * n, b >> 32, tag);
     }
     // the words are loaded before any is tested (one memory round trip per attempt)
-    __device__ static bool get(const uint64_t* p, uint32_t tag, double2& v) {
-        const uint64_t w0 = ld_tag(p + 0), w1 = ld_tag(p + 1), w2 = ld_tag(p + 2);
+    __device__ static bool get(const uint64_t* p, uint32_t tag, double2& v, int n = 1) {
+        const uint64_t w0 = ld_tag(p + 0), w1 = ld_tag(p + n), w2 = ld_tag(p + 2 * n);
         const uint64_t t = (uint64_t)(tag & 0xffffu);
         const bool ok = ((w0 >> 48) == t) & ((w1 >> 48) == t) & ((w2 >> 48) == t);
         const uint64_t m = 0xffffffffffffull;
@@ -56,12 +58,12 @@ template <> struct Tagged<double> {
 };
 template <> struct Tagged<float> {              // complex64: two words
     static constexpr int NW = 2;
-    __device__ static void put(uint64_t* p, float2 v, uint32_t tag) {
+    __device__ static void put(uint64_t* p, float2 v, uint32_t tag, int n = 1) {
         st_tag(p + 0, __float_as_uint(v.x), tag);
-        st_tag(p + 1, __float_as_uint(v.y), tag);
+        st_tag(p + n, __float_as_uint(v.y), tag);
     }
-    __device__ static bool get(const uint64_t* p, uint32_t tag, float2& v) {
-        const uint64_t w0 = ld_tag(p + 0), w1 = ld_tag(p + 1);
+    __device__ static bool get(const uint64_t* p, uint32_t tag, float2& v, int n = 1) {
+        const uint64_t w0 = ld_tag(p + 0), w1 = ld_tag(p + n);
         const bool ok = ((uint32_t)(w0 >> 32) == tag) & ((uint32_t)(w1 >> 32) == tag);
         v.x = __uint_as_float((uint32_t)w0);
         v.y = __uint_as_float((uint32_t)w1);
