@@ -46,6 +46,8 @@
 //    polls out of the tile waves also keeps the tile stream off the critical path.
 #include "la_common.hpp"
 
+#include <type_traits>
+
 namespace cdm {
 
 template <typename T, int KP, int RPL, class Src>
@@ -182,9 +184,11 @@ __global__ __launch_bounds__((la_threads<T, KP>()), 1) void k_cd_panel_la(PanelA
         auto load_tile = [&](Raw(&dst)[NC][RPL], int K) __attribute__((always_inline)) { load_part(dst, K, 0, 8); };
         // A workgroup's memory operations complete in about the order of their issue, so the
         // control wave's words wait behind a panel's 64 KB where they are asked for at once.
-        // complex128: in four pieces over the step, kept apart by scheduling barriers
-        // (16384 x 8192: 51.1 -> 46.7 ms; halves 49.1, all after the partials 53.7).
-        constexpr bool PACED = !OWN_DELTA;
+        // The caller's H comes in pieces over the step, kept apart by scheduling barriers (16384 x
+        // 8192 complex128: 51.1 -> 46.7 ms; halves 49.1, all after the partials 53.7; complex64, 20
+        // sweeps 11.85 -> 11.48 ms).  The small BF16 and FP8 copies come at once (48.1 and 47.4
+        // ms a solve; in pieces 53.0 and 53.7).
+        constexpr bool PACED = std::is_same_v<Src, SrcC<T>>;
         auto load_piece = [&](Raw(&dst)[NC][RPL], int K, int e0, int e1) __attribute__((always_inline)) {
             if constexpr (PACED) {
                 __builtin_amdgcn_sched_barrier(0);
@@ -271,7 +275,8 @@ __global__ __launch_bounds__((la_threads<T, KP>()), 1) void k_cd_panel_la(PanelA
 #define CDM_LA_TSTEP(cur, nn)                                                                         \
     {                                                                                                 \
         if (!wait_b(q)) goto tdone;                                                                   \
-        load_piece(nn, (K + 2) % np, 5, 7); /* the rest of panel K+2, which the last step began */   \
+        /* the rest of panel K+2, which the last step began */                                        \
+        load_piece(nn, (K + 2) % np, 5, OWN_DELTA ? 8 : 7);                                           \
         if constexpr (OWN_DELTA) {                                                                    \
             /* delta of this wave's columns j = wu NC + c; column v of the packed M holds rows        \
                v..KP-1 at offset v KP - v(v-1)/2.  LOCALB: b = q_K - X_K delta_{K-1}, so              \
