@@ -10,7 +10,7 @@
 // powers of two to norms in [1/2, 1), so that every partial sum is at most 1 in magnitude
 // (Cauchy-Schwarz), and the products are rounded to multiples of 2^-61.  That error, at most
 // sqrt(n) 2^-62 of ||h_u|| ||h_v||, is below the rounding of the products themselves.
-// Bound: LDS atomics and the L2 reads of the rows; 16384 x 8192 at 1 % (1.1e8 products) 849 us.
+// Bound: LDS atomics and the L2 reads of the rows; 16384 x 8192 at 1 % (1.1e8 products) 565 us.
 #include "gs.hpp"
 #include "la_common.hpp"
 
@@ -58,13 +58,15 @@ __global__ __launch_bounds__(256) void k_gsp_values(const cv<T>* __restrict__ va
 }
 
 // Row u of G into A (Up x Up, zero past U).  16 waves: each takes every 16th entry of column
-// u and goes through that entry's row, the next row's entries in flight.
+// u and goes through that entry's row, the first 128 entries of the next RING rows in flight (with one
+// row of 64 in flight the round trips took 849 us at 16384 x 8192, 1 %).
 __global__ __launch_bounds__(1024) void k_gsp_matrix(const int32_t* __restrict__ colptr,
                                                      const int32_t* __restrict__ rowidx,
                                                      const int32_t* __restrict__ rowptr,
                                                      const int32_t* __restrict__ colidx,
                                                      const double2* __restrict__ vs, const int32_t* __restrict__ kexp,
                                                      int U, int Up, double2* __restrict__ A) {
+    constexpr int RING = 3;
     extern __shared__ __attribute__((aligned(16))) longlong2 acc[];
     const int u = blockIdx.x, lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     double2* out = A + (int64_t)u * Up;
@@ -72,64 +74,68 @@ __global__ __launch_bounds__(1024) void k_gsp_matrix(const int32_t* __restrict__
         for (int v = threadIdx.x; v < Up; v += 1024) out[v] = make_double2(0.0, 0.0);
         return;
     }
+    const int e0 = colptr[u], e1 = colptr[u + 1];
     for (int v = threadIdx.x; v < U; v += 1024) acc[v] = longlong2{0, 0};
     __syncthreads();
-    const int e0 = colptr[u], e1 = colptr[u + 1];
-    // this wave's entries, a lane each: the row's bounds, and where column u stands in it (its
-    // scaled value is read from the row, as its neighbours are)
+    auto add = [&](int v, const double2& hu, const double2& h) __attribute__((always_inline)) {
+        // conj(h_u) h_v as multiples of 2^-61
+        const double re = fma(hu.x, h.x, hu.y * h.y), im = fma(hu.x, h.y, -(hu.y * h.x));
+        atomicAdd((unsigned long long*)&acc[v].x, (unsigned long long)llrint(re * 0x1p61));
+        atomicAdd((unsigned long long*)&acc[v].y, (unsigned long long)llrint(im * 0x1p61));
+    };
+    auto from_lane = [&](const double2& h, uint64_t mine) __attribute__((always_inline)) -> double2 {
+        const int at = __ffsll((unsigned long long)mine) - 1;
+        return make_double2(lane_value(h.x, at), lane_value(h.y, at));
+    };
+    // this wave's entries, a lane each: the row's bounds
     for (int base = e0 + wid; base < e1; base += 16 * 64) {
         const int e = base + 16 * lane;
-        const bool in = e < e1;
-        const int row = in ? rowidx[e] : 0;
-        const int a0 = in ? rowptr[row] : 0, a1 = in ? rowptr[row + 1] : 0;
+        const int row = e < e1 ? rowidx[e] : 0;
+        const int a0 = e < e1 ? rowptr[row] : 0, a1 = e < e1 ? rowptr[row + 1] : 0;
         const int cnt = min(64, (e1 - base + 15) / 16);
-        int b0 = __builtin_amdgcn_readlane(a0, 0), b1 = __builtin_amdgcn_readlane(a1, 0);
-        int v = -1;
-        double2 h = make_double2(0.0, 0.0);
-        if (b0 + lane < b1) {
-            v = colidx[b0 + lane];
-            h = vs[b0 + lane];
-        }
-        for (int j = 0; j < cnt; ++j) {
-            int vc = v;
-            double2 hc = h;
-            const int c0 = b0, c1 = b1;
-            if (j + 1 < cnt) {   // the next row's first 64 entries
-                b0 = __builtin_amdgcn_readlane(a0, j + 1);
-                b1 = __builtin_amdgcn_readlane(a1, j + 1);
-                v = -1;
-                if (b0 + lane < b1) {
-                    v = colidx[b0 + lane];
-                    h = vs[b0 + lane];
+        int v[RING][2];
+        double2 h[RING][2];
+        auto fetch = [&](int d, int j) __attribute__((always_inline)) {
+            if (j >= cnt) return;
+            const int b0 = __builtin_amdgcn_readlane(a0, j), b1 = __builtin_amdgcn_readlane(a1, j);
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const int k = b0 + lane + 64 * c;
+                v[d][c] = -1;
+                h[d][c] = make_double2(0.0, 0.0);
+                if (k < b1) {
+                    v[d][c] = colidx[k];
+                    h[d][c] = vs[k];
                 }
             }
-            // column u's own entry of this row
-            double2 hu = make_double2(0.0, 0.0);
-            for (int k = c0, w = vc;; k += 64) {
-                if (k != c0) w = k + lane < c1 ? colidx[k + lane] : -1;
-                const uint64_t mine = __ballot(w == u);
-                if (mine) {
-                    const double2 t = k == c0 ? hc : (k + lane < c1 ? vs[k + lane] : hc);
-                    const int at = __ffsll((unsigned long long)mine) - 1;
-                    hu = make_double2(lane_value(t.x, at), lane_value(t.y, at));
-                    break;
-                }
-                if (k + 64 >= c1) break;
-            }
-            for (int k = c0;;) {
-                if (vc >= 0) {
-                    // conj(h_u) h_v as multiples of 2^-61
-                    const double re = fma(hu.x, hc.x, hu.y * hc.y), im = fma(hu.x, hc.y, -(hu.y * hc.x));
-                    atomicAdd((unsigned long long*)&acc[vc].x, (unsigned long long)llrint(re * 0x1p61));
-                    atomicAdd((unsigned long long*)&acc[vc].y, (unsigned long long)llrint(im * 0x1p61));
-                }
-                k += 64;
-                if (k >= c1) break;
-                vc = -1;
-                if (k + lane < c1) {
-                    vc = colidx[k + lane];
-                    hc = vs[k + lane];
-                }
+        };
+#pragma unroll
+        for (int d = 0; d < RING; ++d) fetch(d, d);
+        for (int j0 = 0; j0 < cnt; j0 += RING) {
+#pragma unroll
+            for (int d = 0; d < RING; ++d) {
+                if (j0 + d >= cnt) continue;
+                const int b0 = __builtin_amdgcn_readlane(a0, j0 + d), b1 = __builtin_amdgcn_readlane(a1, j0 + d);
+                // column u's own (scaled) entry of this row
+                double2 hu = make_double2(0.0, 0.0);
+                const uint64_t m0 = __ballot(v[d][0] == u), m1 = __ballot(v[d][1] == u);
+                if (m0)
+                    hu = from_lane(h[d][0], m0);
+                else if (m1)
+                    hu = from_lane(h[d][1], m1);
+                else
+                    for (int k = b0 + 128; k < b1; k += 64) {
+                        const bool in = k + lane < b1;
+                        const uint64_t m = __ballot(in && colidx[in ? k + lane : k] == u);
+                        if (m) {
+                            hu = from_lane(vs[in ? k + lane : k], m);
+                            break;
+                        }
+                    }
+                if (v[d][0] >= 0) add(v[d][0], hu, h[d][0]);
+                if (v[d][1] >= 0) add(v[d][1], hu, h[d][1]);
+                for (int k = b0 + 128 + lane; k < b1; k += 64) add(colidx[k], hu, vs[k]);
+                fetch(d, j0 + d + RING);
             }
         }
     }
